@@ -348,9 +348,17 @@ hipError_t timed(const char *name, double bytes, double ops, F &&fn) {
 
 double words8(uint64_t bits) { return (double)((bits + 63) / 64) * 8.0; }
 
-// P1 over nsrc sources of njobs jobs (bits read: the packed inputs).
+// P1 over nsrc sources of njobs jobs (bits read: the packed inputs).  The
+// operations of the split form's P1 and P3 are word XORs (every word of a
+// chunk enters the sums of each first-step residue, then of each point of
+// the second step); those of its P2 are binary multiply-adds.
 hipError_t p1(const pa::PlanRef &p, int nsrc, const pa::JobArgs &ja, int njobs, double in_bytes, hipStream_t s) {
     const double L = (double)p.host->L;
+    if (p.gf.form == pa::kGfSplit) {
+        const double sw = (double)p.gf.spectrum_words(), P = p.gf.T == 729 ? 27.0 : 9.0;
+        return timed("colfwd", in_bytes + 4.0 * sw * nsrc * njobs, nsrc * njobs * sw * (0.5 * p.gf.T / P + P),
+                     [&](hipEvent_t a, hipEvent_t b) { return pa::launch_gf_fwd(p.gf, nsrc, ja, njobs, s, a, b); });
+    }
     const double bytes = in_bytes + 4.0 * L * nsrc * njobs;
     const double ops = (double)nsrc * njobs * (xform_ops(p.host->col) * p.host->C + kColTwistOps * L);
     return timed("colfwd", bytes, ops,
@@ -360,6 +368,14 @@ hipError_t p1(const pa::PlanRef &p, int nsrc, const pa::JobArgs &ja, int njobs, 
 // P2 in the given mode (0 plan, 1 seed spectrum, 2 fused plain path).
 hipError_t p2(const pa::PlanRef &p, int mode, const pa::JobArgs &ja, int njobs, hipStream_t s) {
     const double L = (double)p.host->L;
+    if (p.gf.form == pa::kGfSplit) {
+        if (mode == 1) return hipSuccess;  // P1's output is the spectrum
+        const double T = p.gf.T, leaf = 64.0 * p.gf.M2, points = 2.0 * p.gf.chunk_words() / p.gf.M2;
+        return timed("rowconv", njobs * 4.0 * (2.0 * p.gf.spectrum_words() + 1.5 * p.gf.spectrum_words()),
+                     njobs * 2.0 * T * points * leaf * leaf, [&](hipEvent_t a, hipEvent_t b) {
+                         return pa::launch_gf_mul(p.gf, mode == 0, ja, njobs, s, a, b);
+                     });
+    }
     const double xf = xform_ops(p.host->row) * p.host->R;
     double bytes = 0, ops = 0;
     if (mode == 1) {
@@ -377,6 +393,10 @@ hipError_t p2(const pa::PlanRef &p, int mode, const pa::JobArgs &ja, int njobs, 
 // P3 of njobs jobs (out_bytes: the packed outputs).
 hipError_t p3(const pa::PlanRef &p, const pa::JobArgs &ja, int njobs, double out_bytes, hipStream_t s) {
     const double L = (double)p.host->L;
+    if (p.gf.form == pa::kGfSplit)
+        return timed("colinv", 4.0 * 1.5 * (double)p.gf.spectrum_words() * njobs + out_bytes,
+                     out_bytes / 4.0 * p.gf.T,
+                     [&](hipEvent_t a, hipEvent_t b) { return pa::launch_gf_inv(p.gf, ja, njobs, s, a, b); });
     const double bytes = 4.0 * L * njobs + out_bytes;
     const double ops = njobs * (xform_ops(p.host->col) * p.host->C + 4.0 * L);
     return timed("colinv", bytes, ops,
@@ -418,6 +438,25 @@ pa::JobDesc modified_job(const uint64_t *key, uint64_t n, const uint64_t *v, uin
 // rows in LDS) when they fit, else the seed spectrum goes through HBM.
 pa_status run_plain(const pa::PlanRef &p, const pa::JobArgs &ja, int njobs, double in_bytes, double out_bytes,
                     hipStream_t s) {
+    if (p.gf.form == pa::kGfDirect) {
+        // n = the key's bits, from the two inputs' total of about 2 n + m
+        const double bits = 8.0 * in_bytes - 8.0 * out_bytes, parts = 4.0 * (double)gf_direct_words(p.gf) * njobs;
+        PA_HIP(timed("direct", in_bytes + (p.gf.slices > 1 ? parts : out_bytes),
+                     bits / njobs * 8.0 * out_bytes,
+                     [&](hipEvent_t a, hipEvent_t b) { return pa::launch_gf_direct(p.gf, ja, njobs, s, a, b); }),
+               "launch direct product");
+        if (p.gf.slices > 1)
+            PA_HIP(timed("parts", parts + out_bytes, parts / 4.0,
+                         [&](hipEvent_t a, hipEvent_t b) { return pa::launch_gf_parts(p.gf, ja, njobs, s, a, b); }),
+                   "launch slice sum");
+        return PA_OK;
+    }
+    if (p.gf.form == pa::kGfSplit) {
+        PA_HIP(p1(p, 2, ja, njobs, in_bytes, s), "launch P1");
+        PA_HIP(p2(p, 2, ja, njobs, s), "launch P2");
+        PA_HIP(p3(p, ja, njobs, out_bytes, s), "launch P3");
+        return PA_OK;
+    }
     PA_HIP(p1(p, 2, ja, njobs, in_bytes, s), "launch P1");
     if (p.host->fused_ok) {
         PA_HIP(p2(p, 2, ja, njobs, s), "launch P2");
@@ -472,6 +511,18 @@ pa_status plan_cached(uint64_t L, int cls, pa::PlanRef *lp) {
     return PA_OK;
 }
 
+// Words of the areas A and S of a block in the plan's form.
+uint64_t area_words_a(const pa::PlanRef &p) {
+    if (p.gf.form == pa::kGfDirect) return (gf_direct_words(p.gf) + 63) / 64 * 64;
+    if (p.gf.form == pa::kGfSplit) return (p.gf.work_words() + 63) / 64 * 64;
+    return p.host->L;
+}
+uint64_t area_words_s(const pa::PlanRef &p) {
+    if (p.gf.form == pa::kGfDirect) return 0;
+    if (p.gf.form == pa::kGfSplit) return (p.gf.spectrum_words() + 63) / 64 * 64;
+    return p.host->L;
+}
+
 // Key path against a ready spectrum Shat: P1 (key), P2 (convolve), P3.
 pa_status run_key_path(const pa::PlanRef &p, const uint64_t *key, uint64_t n, uint64_t m, const int32_t *Shat,
                        int32_t *A, uint64_t *out, hipStream_t s) {
@@ -501,11 +552,13 @@ pa_status hash_one(const uint64_t *key, uint64_t n, const uint64_t *seed, uint64
                    hipStream_t s) {
     pa::PlanRef p{};
     PA_TRY(plan_for(L, 0, &p));
+    if (gf_allowed(p)) p.gf = pa::gf_plain_for(n, m, pa::required_len(n, m), UINT64_MAX, 1);
+    const uint64_t wa = area_words_a(p), wsd = area_words_s(p);
     void *ws = nullptr;
     std::unique_lock<std::mutex> ws_hold;
-    PA_TRY(get_workspace(s, (size_t)(8 * L), &ws, &ws_hold));
+    PA_TRY(get_workspace(s, (size_t)std::max<uint64_t>(4 * (wa + wsd), 256), &ws, &ws_hold));
     pa::JobArgs ja{};
-    ja.one = plain_job(key, n, seed, m, out, (int32_t *)ws, (int32_t *)ws + L);
+    ja.one = plain_job(key, n, seed, m, out, (int32_t *)ws, (int32_t *)ws + wa);
     return run_plain(p, ja, 1, words8(n) + words8(n + m - 1), words8(m), s);
 }
 
@@ -518,7 +571,8 @@ struct pa_plan_s {
     int device = 0;
     uint64_t L = 0;
     uint64_t seed_len = 0;
-    int32_t *Shat = nullptr;
+    int32_t *Shat = nullptr;     // spectrum in lp's form; the plan's allocation
+    uint64_t *seed = nullptr;    // carry-less form: the seed's first min(seed_len, L) bits, after Shat
     pa::PlanRef lp{};
 };
 
@@ -651,11 +705,13 @@ pa_status pa_modified_toeplitz_hash(const uint64_t *key_bits, uint64_t n, const 
     hipStream_t s = (hipStream_t)stream;
     pa::PlanRef p{};
     PA_TRY(plan_for(L, 0, &p));
+    if (gf_allowed(p)) p.gf = pa::gf_plain_for(n - m, m, pa::required_len(n - m, m), UINT64_MAX, 1);
+    const uint64_t wa = area_words_a(p), wsd = area_words_s(p);
     void *ws = nullptr;
     std::unique_lock<std::mutex> ws_hold;
-    PA_TRY(get_workspace(s, (size_t)(8 * L), &ws, &ws_hold));
+    PA_TRY(get_workspace(s, (size_t)std::max<uint64_t>(4 * (wa + wsd), 256), &ws, &ws_hold));
     pa::JobArgs ja{};
-    ja.one = modified_job(key_bits, n, v_bits, m, out_bits, (int32_t *)ws, (int32_t *)ws + L);
+    ja.one = modified_job(key_bits, n, v_bits, m, out_bits, (int32_t *)ws, (int32_t *)ws + wa);
     return run_plain(p, ja, 1, words8(n) + words8(n - 1) + words8(m), words8(m), s);
 }
 
@@ -716,9 +772,11 @@ std::vector<std::vector<PassGroup>> form_classes(std::vector<PassGroup> v, Wgs w
 
 // Validation, length groups and plans of a block array (host only), and
 // the flat form's launch classes.
-pa_status prepare_batch(const pa_block *blocks, uint32_t count, bool modified, BatchPrep *bp, BatchForm form) {
+pa_status prepare_batch(const pa_block *blocks, uint32_t count, bool modified, BatchPrep *bp, BatchForm form,
+                        bool any_sizes) {
     if (!blocks) return fail(PA_ERR_INVALID_ARG, "null block array");
     bp->modified = modified;
+    bp->any_sizes = any_sizes;
     bp->form = form;
     bp->blocks.assign(blocks, blocks + count);
     bp->block_len.assign(count, 0);
@@ -738,6 +796,18 @@ pa_status prepare_batch(const pa_block *blocks, uint32_t count, bool modified, B
         gr.L = g.first;
         gr.members = g.second;
         PA_TRY(plan_for(g.first, g.second.size() > 1 ? 1 : 0, &gr.plan));
+        if (form == kFormLanes && gf_allowed(gr.plan)) {
+            uint64_t n = 0, m = 0, bits = 0;
+            for (uint32_t i : gr.members) {
+                const uint64_t kn = modified ? blocks[i].n - blocks[i].m : blocks[i].n;
+                n = std::max(n, kn);
+                m = std::max(m, blocks[i].m);
+                bits = std::max(bits, pa::required_len(kn, blocks[i].m));
+            }
+            // a graph's launches keep room for the longest blocks of the length
+            gr.plan.gf = pa::gf_plain_for(n, m, any_sizes ? gr.L : bits, UINT64_MAX, (int)gr.members.size());
+            if (any_sizes) gr.plan.gf.max_m = (uint32_t)(modified ? gr.L : gr.L / 2 + 64);
+        }
         if (form == kFormLanes) {
             // seeds shared by several members of the group (same device
             // pointer and bit count, so the same spectrum), in first-use order
@@ -842,13 +912,14 @@ pa_status prepare_batch(const pa_block *blocks, uint32_t count, bool modified, B
         PA_TRY(add(2, form_classes(p2, roww)));
         PA_TRY(add(3, form_classes(p3, colw(true))));
     }
-    // workspace: the table region, then 8L bytes (A and S) per plain-path
-    // block, 4L (A) per block sharing a seed and 4L per shared spectrum
+    // workspace: the table region, then A and S per plain-path block, A per
+    // block sharing a seed and S per shared spectrum
     bp->table_bytes = (region + 255) / 256 * 256;
     bp->total_bytes = bp->table_bytes;
     for (const auto &g : bp->groups) {
-        bp->total_bytes += (size_t)(8 * g.L) * g.plain.size();
-        for (const auto &sh : g.shared) bp->total_bytes += (size_t)(4 * g.L) * (sh.size() + 1);
+        const uint64_t a = 4 * area_words_a(g.plan), sp = 4 * area_words_s(g.plan);
+        bp->total_bytes += (size_t)(a + sp) * g.plain.size();
+        for (const auto &sh : g.shared) bp->total_bytes += (size_t)(a * sh.size() + sp);
     }
     return PA_OK;
 }
@@ -866,24 +937,26 @@ void build_table(BatchPrep &bp, void *ws) {
                            : plain_job(b.key_bits, b.n, b.seed_bits, b.m, b.out_bits, A, S);
     };
     for (auto &g : bp.groups) {
+        const uint64_t a = area_words_a(g.plan), sp = area_words_s(g.plan);
+        const bool direct = g.plan.gf.form == pa::kGfDirect;
         g.first = bp.table.size();
         for (uint32_t i : g.plain) {
-            desc[i] = job(i, next, next + g.L);
-            next += 2 * g.L;
+            desc[i] = job(i, next, next + a);
+            next += a + sp;
             bp.table.push_back(desc[i]);
         }
         g.first_shared = bp.table.size();
         std::vector<int32_t *> spec(g.shared.size());
         for (size_t k = 0; k < g.shared.size(); ++k) {
             spec[k] = next;
-            next += g.L;
+            next += sp;
         }
         for (size_t k = 0; k < g.shared.size(); ++k)
             for (uint32_t i : g.shared[k]) {
                 desc[i] = job(i, next, nullptr);
-                desc[i].seed = nullptr;
+                if (!direct) desc[i].seed = nullptr;
                 desc[i].Shat = spec[k];
-                next += g.L;
+                next += a;
                 bp.table.push_back(desc[i]);
             }
         g.first_spec = bp.table.size();
@@ -1022,10 +1095,14 @@ pa_status launch_batch(const BatchPrep &bp, void *ws, hipStream_t s) {
     for (int gi : order) {
         const BatchPrep::Group &g = bp.groups[gi];
         const hipStream_t ls = lane_s[lane_of[gi]];
-        chunks(g.first, g.plain.size(), [&](const pa::JobArgs &ja, int nj, double in_b, double out_b) {
+        size_t plain = g.plain.size();
+        const bool direct = g.plan.gf.form == pa::kGfDirect;
+        if (direct)  // no spectra: the blocks that share seeds follow in the table
+            for (const auto &sh : g.shared) plain += sh.size();
+        chunks(g.first, plain, [&](const pa::JobArgs &ja, int nj, double in_b, double out_b) {
             return run_plain(g.plan, ja, nj, in_b, out_b, ls);
         });
-        if (!g.shared.empty()) {
+        if (!direct && !g.shared.empty()) {
             // the shared seeds' spectra, then their members' key path
             size_t nsh = 0;
             for (const auto &sh : g.shared) nsh += sh.size();
@@ -1088,8 +1165,15 @@ pa_status pa_plan_create(const uint64_t *seed_bits, uint64_t seed_len_bits, uint
     PA_TRY(plan_for(L, 0, &lp));
     pa_plan_s *p = new (std::nothrow) pa_plan_s();
     if (!p) return fail(PA_ERR_OUT_OF_MEMORY, "host allocation");
+    const uint64_t used = std::min(seed_len_bits, L);
+    // Every block that the plan takes ends within n + m - 1 <= seed_len
+    // bits and its required length within L; seed bits past the cyclic
+    // length would wrap onto outputs.
+    if (gf_allowed(lp)) lp.gf = pa::gf_split_for(std::min(L, seed_len_bits + 126), UINT64_MAX);
+    const bool gf = lp.gf.form != pa::kGfNone;
+    const size_t spec = (size_t)(4 * area_words_s(lp));
     hipError_t e = hipGetDevice(&p->device);
-    if (e == hipSuccess) e = hipMalloc((void **)&p->Shat, (size_t)(4 * L));
+    if (e == hipSuccess) e = hipMalloc((void **)&p->Shat, spec + (gf ? (size_t)words8(used) : 0));
     if (e != hipSuccess) {
         delete p;
         return from_hip(e, "plan allocation");
@@ -1097,7 +1181,12 @@ pa_status pa_plan_create(const uint64_t *seed_bits, uint64_t seed_len_bits, uint
     p->L = L;
     p->seed_len = seed_len_bits;
     p->lp = lp;
-    pa_status st = run_seed_path(lp, seed_bits, std::min(seed_len_bits, L), p->Shat, (hipStream_t)stream);
+    if (gf) {
+        p->seed = (uint64_t *)((char *)p->Shat + spec);
+        e = hipMemcpyAsync(p->seed, seed_bits, (size_t)words8(used), hipMemcpyDeviceToDevice, (hipStream_t)stream);
+    }
+    pa_status st = e != hipSuccess ? from_hip(e, "plan seed copy")
+                                   : run_seed_path(lp, seed_bits, used, p->Shat, (hipStream_t)stream);
     if (st != PA_OK) {
         (void)hipFree(p->Shat);
         delete p;
@@ -1122,8 +1211,20 @@ pa_status pa_plan_hash(pa_plan_t plan, const uint64_t *key_bits, uint64_t n, uin
     if (dev != plan->device) return fail(PA_ERR_INVALID_ARG, "plan belongs to another device");
     void *ws = nullptr;
     std::unique_lock<std::mutex> ws_hold;
-    PA_TRY(get_workspace((hipStream_t)stream, (size_t)(4 * plan->L), &ws, &ws_hold));
-    return run_key_path(plan->lp, key_bits, n, m, plan->Shat, (int32_t *)ws, out_bits, (hipStream_t)stream);
+    pa::PlanRef p = plan->lp;
+    if (plan->seed) {
+        // a short block's product with the seed bits themselves is faster
+        const pa::GfChoice c = pa::gf_plain_for(n, m, plan->L, UINT64_MAX, 1);
+        if (c.form == pa::kGfDirect) p.gf = c;
+        p.gf.max_m = (uint32_t)m;
+    }
+    PA_TRY(get_workspace((hipStream_t)stream, (size_t)std::max<uint64_t>(4 * area_words_a(p), 256), &ws, &ws_hold));
+    if (p.gf.form == pa::kGfDirect) {
+        pa::JobArgs ja{};
+        ja.one = plain_job(key_bits, n, plan->seed, m, out_bits, (int32_t *)ws, nullptr);
+        return run_plain(p, ja, 1, words8(n) + words8(n + m - 1), words8(m), (hipStream_t)stream);
+    }
+    return run_key_path(p, key_bits, n, m, plan->Shat, (int32_t *)ws, out_bits, (hipStream_t)stream);
 }
 
 pa_status pa_plan_spectrum(pa_plan_t plan, int32_t *out, void *stream) {
@@ -1131,6 +1232,12 @@ pa_status pa_plan_spectrum(pa_plan_t plan, int32_t *out, void *stream) {
     int dev = 0;
     PA_HIP(hipGetDevice(&dev), "hipGetDevice");
     if (dev != plan->device) return fail(PA_ERR_INVALID_ARG, "plan belongs to another device");
+    if (plan->seed) {
+        // the plan keeps a carry-less spectrum: transform the seed's copy in out
+        pa::PlanRef p = plan->lp;
+        p.gf = pa::GfChoice{};
+        return run_seed_path(p, plan->seed, std::min(plan->seed_len, plan->L), out, (hipStream_t)stream);
+    }
     PA_HIP(hipMemcpyAsync(out, plan->Shat, (size_t)(4 * plan->L), hipMemcpyDeviceToDevice, (hipStream_t)stream),
            "spectrum copy");
     return PA_OK;

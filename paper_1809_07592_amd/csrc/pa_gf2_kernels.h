@@ -1,0 +1,687 @@
+// gfx950 kernels of the carry-less forms (see pa_gf2.h).  Included by
+// pa_kernels.hip, whose buffer and job helpers they use.
+#pragma once
+
+#include "pa_gf2.h"
+
+namespace pa {
+
+typedef int gf_v4i __attribute__((ext_vector_type(4)));
+typedef int gf_v8i __attribute__((ext_vector_type(8)));
+typedef float gf_v4f __attribute__((ext_vector_type(4)));
+
+// 32 bits from bit `sh` (0..31) of the 64-bit value (hi, lo).
+__device__ __forceinline__ uint32_t funnel(uint32_t hi, uint32_t lo, uint32_t sh) {
+    return __builtin_amdgcn_alignbit(hi, lo, sh);
+}
+
+// The word after byte offset o, which may be negative: the sum is formed in
+// the register, since a hardware offset added to a negative one is out of
+// range.
+__device__ __forceinline__ uint32_t ld32_next(rsrc_t r, int o) {
+    int k = o + 4;
+    asm("" : "+v"(k));
+    return (uint32_t)ld32(r, k);
+}
+
+// One 16 x 16 x 128 binary product on the matrix cores: the operands hold
+// one bit per fp4 element, A's ones as 1.0 and B's as 0.5, so an
+// accumulator is half the count of common ones (exact in fp32 below 2^23)
+// and its fraction the parity.  Lane l holds 32 consecutive k of row
+// (column) l & 15 from k = 32 (l >> 4), as one 32-bit window; bit 4 p + j
+// goes to nibble p of register j, in both operands alike.
+__device__ __forceinline__ gf_v4i expand_a(uint32_t w) {
+    gf_v4i r = {(int)((w << 1) & 0x22222222u), (int)(w & 0x22222222u), (int)((w >> 1) & 0x22222222u),
+                (int)((w >> 2) & 0x22222222u)};
+    return r;
+}
+__device__ __forceinline__ gf_v4i expand_b(uint32_t w) {
+    gf_v4i r = {(int)(w & 0x11111111u), (int)((w >> 1) & 0x11111111u), (int)((w >> 2) & 0x11111111u),
+                (int)((w >> 3) & 0x11111111u)};
+    return r;
+}
+__device__ __forceinline__ gf_v4f bit_mfma(gf_v4i a, gf_v4i b, gf_v4f c) {
+    const gf_v8i A = {a[0], a[1], a[2], a[3], 0, 0, 0, 0}, B = {b[0], b[1], b[2], b[3], 0, 0, 0, 0};
+    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A, B, c, 4, 4, 0, 0, 0, 0);
+}
+
+// The parities of one 16 x 16 tile as its 8 words: output bit 16 r + q of
+// row r, column q.  Accumulator v of lane l is row 4 (l >> 4) + v, column
+// l & 15, so ballot v holds row 4 h + v in its 16-bit field h.  Word j goes
+// to lane BASE + j of `into`.
+template <int BASE>
+__device__ __forceinline__ uint32_t tile_words(gf_v4f acc, uint32_t into) {
+    uint64_t b[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) b[v] = __ballot(__builtin_amdgcn_fractf(acc[v]) != 0.0f);
+#pragma unroll
+    for (int h = 0; h < 4; ++h)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const uint32_t lo = (uint32_t)(b[2 * p] >> (16 * h)) & 0xFFFFu;
+            const uint32_t hi = (uint32_t)(b[2 * p + 1] >> (16 * h)) & 0xFFFFu;
+            asm("v_writelane_b32 %0, %1, %2" : "+v"(into) : "s"(lo | (hi << 16)), "i"(BASE + 2 * h + p));
+        }
+    return into;
+}
+
+// Word w of the job's output: bits past m cleared, the head of the key
+// XORed in (modified Toeplitz), words past the last 64-bit word dropped.
+struct OutWords {
+    rsrc_t out, head;
+    uint32_t m;
+    __device__ __forceinline__ OutWords(const JobDesc &job)
+        : out(make_rsrc(job.out, (uint32_t)((job.m + 63) / 64 * 8))),
+          head(make_rsrc(job.xor_src, job.xor_src ? (uint32_t)((job.m + 31) / 32 * 4) : 0u)),
+          m(job.m) {}
+    __device__ __forceinline__ void put(uint32_t w, uint32_t v) const {
+        v ^= (uint32_t)ld32(head, (int)(w * 4));
+        const int keep = (int)m - (int)(w * 32);
+        if (keep < 32) v = keep > 0 ? v & ((1u << keep) - 1u) : 0u;
+        st32(out, (int)(w * 4), (int)v);
+    }
+};
+
+// ------------------------------------------------------------------- direct
+//
+// y[i] = sum_j s[i - j + n - 1] x[j].  With xr the reversed key and
+// i = 256 R + 16 r + q this is sum_k s[256 R + 16 r + k] xr[k - q]: a matrix
+// product whose row operand starts at a multiple of 16 bits of the seed and
+// whose column operand is the key shifted by its column, so both are 32-bit
+// windows of packed bits, expanded in registers.  A workgroup computes NT
+// tiles of 256 outputs; its waves (and the launch's slices) share k.  The
+// row operand depends on k + 256 R only: a step of k = 128 needs one new
+// row fragment for all NT tiles (the others are those of earlier steps, kept
+// in 2 NT rotating registers) and one column fragment.
+template <int NT, bool PARTS>
+__global__ void __launch_bounds__(512) k_gf_direct(JobArgs ja) {
+    constexpr int U = 2 * NT;  // steps per unrolled unit
+    const JobDesc job = job_of(ja, uni(blockIdx.z));
+    const int n = (int)job.n, R0 = (int)blockIdx.x * NT;
+    if ((uint32_t)R0 * 256u >= job.m) return;
+    const int lane = threadIdx.x & 63, wave = (int)uni(threadIdx.x >> 6), nw = blockDim.x >> 6;
+    const int q = lane & 15, kb = lane >> 4;
+    const int steps = (n + 15 + 127) / 128, units = (steps + U - 1) / U;
+    const int share = (int)gridDim.y * nw, per = (units + share - 1) / share;
+    const int u0 = min(units, ((int)blockIdx.y * nw + wave) * per), u1 = min(units, u0 + per);
+
+    const rsrc_t sb = make_rsrc(job.seed, (uint32_t)((job.seed_bits + 31) / 32 * 4));
+    const int ko = (int)(job.key_off & 31u), last = (ko + n - 1) >> 5;
+    const rsrc_t xb = make_rsrc((const uint32_t *)job.key + (job.key_off >> 5), (uint32_t)(last + 1) * 4);
+    // seed window of fragment f: word 8 R0 + 4 f + kb + (r >> 1), odd rows
+    // 16 bits on; key window of step k: bits from x0 - 128 k - 32 kb,
+    // reversed
+    const int aoff = (8 * R0 + kb + (q >> 1)) * 4;
+    const uint32_t ash = 16u * (uint32_t)(q & 1);
+    const int x0 = n + ko - 32 + q;
+    const int bw = (x0 >> 5) - kb;
+    const uint32_t bsh = (uint32_t)x0 & 31u;
+    const uint32_t first_mask = ~0u << ko, last_mask = ~0u >> (31 - ((ko + n - 1) & 31));
+
+    auto fetch_a = [&](int f) PA_INLINE {
+        const uint32_t lo = (uint32_t)ld32(sb, aoff + f * 16), hi = (uint32_t)ld32(sb, aoff + f * 16 + 4);
+        return funnel(hi, lo, ash);
+    };
+    auto fetch_b = [&](int k, bool edge) PA_INLINE {
+        const int w = bw - 4 * k;
+        uint32_t lo = (uint32_t)ld32(xb, w * 4), hi;
+        if (!edge) {
+            hi = (uint32_t)ld32(xb, w * 4 + 4);
+        } else {  // uniform: the key's first and last words
+            hi = ld32_next(xb, w * 4);
+            if (w == 0) lo &= first_mask;
+            if (w == last) lo &= last_mask;
+            if (w + 1 == 0) hi &= first_mask;
+            if (w + 1 == last) hi &= last_mask;
+        }
+        return __builtin_bitreverse32(funnel(hi, lo, bsh));
+    };
+    auto is_edge = [&](int u) PA_INLINE { return u == 0 || (u + 1) * (U * 128) + 160 > n; };
+
+    gf_v4f acc[NT] = {};
+    if (u0 < u1) {
+        gf_v4i af[U];
+#pragma unroll
+        for (int f = 0; f < U - 2; ++f) af[f] = expand_a(fetch_a(u0 * U + f));
+        uint32_t aw[U], bwd[U];
+#pragma unroll
+        for (int s = 0; s < U; ++s) {
+            aw[s] = fetch_a(u0 * U + s + U - 2);
+            bwd[s] = fetch_b(u0 * U + s, is_edge(u0));
+        }
+        for (int u = u0; u < u1; ++u) {
+            uint32_t an[U], bn[U];
+            // the next unit's windows (past the end: the buffers' range
+            // check gives zeros, and nothing uses them)
+#pragma unroll
+            for (int s = 0; s < U; ++s) {
+                an[s] = fetch_a((u + 1) * U + s + U - 2);
+                bn[s] = fetch_b((u + 1) * U + s, is_edge(u + 1));
+            }
+#pragma unroll
+            for (int s = 0; s < U; ++s) {
+                af[(s + U - 2) % U] = expand_a(aw[s]);
+                const gf_v4i b = expand_b(bwd[s]);
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[t] = bit_mfma(af[(s + 2 * t) % U], b, acc[t]);
+            }
+#pragma unroll
+            for (int s = 0; s < U; ++s) {
+                aw[s] = an[s];
+                bwd[s] = bn[s];
+            }
+        }
+    }
+    // XOR of the waves' parities, 8 NT words per workgroup
+    __shared__ uint32_t red[8][8 * NT];
+    uint32_t words = 0;
+    static_for_up<0, NT>([&](auto t) PA_INLINE { words = tile_words<8 * t>(acc[t], words); });
+    if (lane < 8 * NT) red[wave][lane] = words;
+    __syncthreads();
+    if (threadIdx.x < 8 * NT) {
+        uint32_t v = 0;
+        for (int w = 0; w < nw; ++w) v ^= red[w][threadIdx.x];
+        const uint32_t wd = (uint32_t)R0 * 8u + threadIdx.x;
+        if constexpr (PARTS) {
+            const uint32_t stride = (job.m + 255u) / 256u * 8u;
+            if (wd < stride) ((uint32_t *)job.A)[(size_t)blockIdx.y * stride + wd] = v;
+        } else {
+            OutWords(job).put(wd, v);
+        }
+    }
+}
+
+// XOR of the slices' partial words into the output.
+__global__ void __launch_bounds__(256) k_gf_parts(JobArgs ja, int slices) {
+    const JobDesc job = job_of(ja, uni(blockIdx.y));
+    const uint32_t w = blockIdx.x * 256u + threadIdx.x, stride = (job.m + 255u) / 256u * 8u;
+    if (w >= stride) return;
+    uint32_t v = 0;
+    for (int i = 0; i < slices; ++i) v ^= ((const uint32_t *)job.A)[(size_t)i * stride + w];
+    OutWords(job).put(w, v);
+}
+
+// -------------------------------------------------------------------- split
+//
+// Ring elements.  In GF(2)[v] / (v^(2M) + v^M + 1), v = X^32, v has order
+// 3 M.  An element (lo, hi) of 2 M words is also the periodic sequence
+// beta = (lo, lo + hi, hi) of 3 M words, and multiplying by v^s rotates
+// beta by s: sums of rotated elements need no reduction.  Two of the three
+// thirds determine the element; a table of five thirds (one period and two
+// more) gives lo and hi of a rotation at a linear index.
+
+// Word W of a bit string taken from bit `off` of base (may be negative: the
+// bits before are zeros), bits outside [lo, hi) of the result cleared.
+struct BitSource {
+    rsrc_t buf;
+    int dw;         // word of bit 0
+    uint32_t rem;   // bit position inside it
+    int lo, hi;     // valid bits
+    __device__ __forceinline__ uint32_t word(int W, bool edge) const {
+        const int i = (W + dw) * 4;
+        uint32_t v = (uint32_t)ld32(buf, i);
+        if (rem) v = funnel(edge ? ld32_next(buf, i) : (uint32_t)ld32(buf, i + 4), v, rem);
+        if (edge) {
+            const int a = lo - 32 * W, b = hi - 32 * W;
+            const uint32_t ma = a <= 0 ? ~0u : a >= 32 ? 0u : ~0u << a;
+            const uint32_t mb = b >= 32 ? ~0u : b <= 0 ? 0u : (1u << b) - 1u;
+            v &= ma & mb;
+        }
+        return v;
+    }
+};
+
+// P1: forward transform of the chunks a_t (M words each, t < T = P Q) at
+// the T-th root v^g:  X_tau = sum_t v^(g tau t) a_t.  With tau = rho + Q
+// sigma and t = t0 + P t1 the inner sums over t1 are formed by scattering
+// every chunk, rotated, into tile t0, and a length-P transform over t0
+// follows.  Word positions split into classes modulo Cm = g P that no
+// rotation of the second step leaves; a workgroup takes one rho and F
+// classes (F divides Cm), so its tile is P x Q x F words.
+// Grid: (Q Cm / F, sources, jobs), 9 waves.  Wave w owns tiles t0 = w,
+// w + 9, ...: nothing else writes them before the barrier.
+constexpr int kGfWaves = 9;
+
+template <int Q, int P>
+__global__ void __launch_bounds__(64 * kGfWaves) k_gf_fwd(JobArgs ja, int g, int F) {
+    constexpr int T = P * Q, Q3 = Q / 3;
+    static_assert(P % kGfWaves == 0 && Q % 9 == 0, "tiles are dealt to 9 waves, rows unrolled by 9");
+    const bool src = blockIdx.y != 0;
+    const JobDesc job = job_of(ja, uni(blockIdx.z));
+    const int M = T / 3 * g, Cm = g * P, nf = Cm / F;
+    const int rho = (int)blockIdx.x / nf, f0 = ((int)blockIdx.x - rho * nf) * F;
+    uint32_t *tile = (uint32_t *)pa_lds;  // [P][5 Q / 3][F]
+    const int trow = 5 * Q3 * F;
+    const int lane = threadIdx.x & 63, wave = (int)uni(threadIdx.x >> 6);
+
+    BitSource in;
+    {
+        const uint64_t *base = src ? job.seed : job.key;
+        const int nbits = (int)(src ? job.seed_bits : job.n);
+        const int shift = src ? 0 : (int)job.shift, off = src ? 0 : (int)job.key_off;
+        // the string starts `shift` bits after position 0 and is read from
+        // bit `off` of the buffer
+        const int d = (off & 31) - shift;
+        const uint32_t *b32 = (const uint32_t *)base + (off >> 5);
+        in.buf = make_rsrc(b32, (uint32_t)(((off & 31) + nbits + 31) / 32 * 4));
+        in.dw = d >> 5;
+        in.rem = (uint32_t)d & 31u;
+        in.lo = shift;
+        in.hi = shift + nbits;
+    }
+    const int rows = min(T, (in.hi + 32 * M - 1) / (32 * M));  // chunks that hold bits
+
+    const int lanes = Q3 * F;  // words of a chunk in the workgroup's classes
+    for (int t0 = wave; t0 < P; t0 += kGfWaves) {
+        uint32_t *tl = tile + t0 * trow;
+        for (int i = lane; i < Q * F; i += 64) tl[i] = 0;
+        const int s0 = (g * rho * t0) % (3 * M), sc = s0 % Cm, si = s0 / Cm;
+        for (int l = lane; l < lanes; l += 64) {
+            const int i1 = l / F, f = l - i1 * F;
+            int c = f0 + f - sc;  // class of the source word
+            const int wrap = c < 0;
+            c += wrap ? Cm : 0;
+            const int e = c + Cm * i1;
+            int ip = i1 + wrap + si;  // row of the target
+            if (ip >= Q) ip -= Q;
+            uint32_t *dst = tl + f;
+            // t1 = 0 .. Q - 1 in groups whose loads are in flight together
+#pragma unroll 1
+            for (int b = 0; b < Q && t0 + P * b < rows; b += 9) {
+                uint32_t w[9];
+#pragma unroll
+                for (int k = 0; k < 9; ++k) {
+                    const int t = t0 + P * (b + k);
+                    w[k] = in.word(t * M + e, t == 0 || t >= rows - 1);
+                }
+#pragma unroll
+                for (int k = 0; k < 9; ++k) {
+                    atomicXor(dst + ip * F, w[k]);
+                    ip += rho;
+                    if (ip >= Q) ip -= Q;
+                }
+            }
+        }
+        // rows to periodic form, five thirds
+        for (int l = lane; l < lanes; l += 64) {
+            const uint32_t a = tl[l], b = tl[l + Q3 * F], c = tl[l + 2 * Q3 * F];
+            tl[l] = a ^ c;
+            tl[l + Q3 * F] = a ^ b;
+            tl[l + 2 * Q3 * F] = b ^ c;
+            tl[l + 3 * Q3 * F] = a ^ c;
+            tl[l + 4 * Q3 * F] = a ^ b;
+        }
+    }
+    __syncthreads();
+    const rsrc_t xo = make_rsrc(src ? job.S : job.A, (uint32_t)(2 * T * M * 4));
+    for (int tk = threadIdx.x; tk < P * lanes; tk += 64 * kGfWaves) {
+        const int sg = tk / lanes, l = tk - sg * lanes;
+        const int i = l / F, f = l - i * F;
+        const int step = Q / P * sg * F;
+        int j = i * F;
+        uint32_t lo = 0, hi = 0;
+#pragma unroll
+        for (int t0 = 0; t0 < P; ++t0) {
+            const uint32_t *tl = tile + t0 * trow + f + j;
+            lo ^= tl[0];
+            hi ^= tl[2 * Q3 * F];
+            j -= step;
+            if (j < 0) j += Q * F;
+        }
+        const int at = ((rho + Q * sg) * 2 * M + i * Cm + f0 + f) * 4;
+        st32(xo, at, (int)lo);
+        st32(xo, at + M * 4, (int)hi);
+    }
+}
+
+// P2: the product of X_tau and S_tau in the ring of 2 M words, and its
+// combination with the next chunk's overlap, one workgroup per (tau, job).
+// An element is a polynomial of 2 * 3^a coefficients of M2 words; its values
+// at the points z = u^i, u = v^(M2 / 3^a) of order 3^(a+1), i not a multiple
+// of 3, in the ring of 2 M2 words are sums of rotated coefficients.  The
+// 2 * 3^a products there are binary Toeplitz products on the matrix cores:
+// with the periodic sequence of one factor, output x is the plain
+// correlation at x for 0 <= x < 64 M2, so no reduction follows.
+template <int A, int M2>
+struct GfMul {
+    static constexpr int NA = A == 1 ? 3 : A == 2 ? 9 : 27;
+    static constexpr int NP = 2 * NA, M = NA * M2, U = M2 / NA;
+    static_assert(M2 % NA == 0, "the unit rotation is a whole number of words");
+    static constexpr int tiles = (64 * M2 + 255) / 256, steps = (64 * M2 + 16 + 127) / 128;
+    // tiles of one sweep over k (their row fragments stay in registers)
+    static constexpr int sweeps = (tiles + 6) / 7, nt = (tiles + sweeps - 1) / sweeps;
+    static constexpr int waves = NP < kGfWaves ? NP : kGfWaves;
+    // LDS (words): five-third tables of X (then the products) and S (then
+    // the waves' expanded row operands), the reversed column operands, and
+    // the row operands
+    static constexpr int table = NP * 5 * M2;
+    static constexpr int units = 16 * nt * sweeps + 8 * steps;  // 16-bit steps of an expanded row operand
+    static constexpr int va = 4 * steps + 2, vb = 4 * M2 + 1;
+    static constexpr int region2 = table > waves * units * 4 ? table : waves * units * 4;
+    static constexpr int off_e = (table + 3) / 4 * 4, off_va = off_e + region2, off_vb = off_va + NP * va;
+    static constexpr int lds_words = off_vb + NP * vb;
+    static_assert(NP * va >= 4 * M, "the inverse transform's output reuses the column operands");
+    static_assert(NP * vb >= 3 * M, "the product reuses the row operands");
+};
+
+template <int A, int M2>
+__global__ void __launch_bounds__((64 * GfMul<A, M2>::waves)) k_gf_mul(JobArgs ja, int T, int g, int resident) {
+    using G = GfMul<A, M2>;
+    constexpr int NA = G::NA, NP = G::NP, M = G::M, U = G::U, NTH = 64 * G::waves;
+    const JobDesc job = job_of(ja, uni(blockIdx.y));
+    const int tau = (int)blockIdx.x, tid = threadIdx.x;
+    const int lane = tid & 63, wave = (int)uni((uint32_t)tid >> 6);
+    uint32_t *lds = (uint32_t *)pa_lds;
+    uint32_t *tx = lds, *ts = lds + G::off_e, *va = lds + G::off_va, *vb = lds + G::off_vb;
+    const int32_t *S = resident ? job.Shat : job.S;
+    const rsrc_t xr = make_rsrc(job.A + (size_t)tau * 2 * M, 2 * M * 4);
+    const rsrc_t sr = make_rsrc(S + (size_t)tau * 2 * M, 2 * M * 4);
+
+    // coefficients c of B_r(z) = element mod (z^NA - v^(r M2)), r = 1, 2, in
+    // five thirds: (lo, lo+hi, hi, ...) and (lo+hi, lo, hi, ...)
+    for (int i = tid; i < 2 * M; i += NTH) {
+        const bool second = i >= M;
+        const int p = second ? i - M : i, c = p / M2, o = p - c * M2;
+        const uint32_t lo = (uint32_t)ld32(second ? sr : xr, p * 4), hi = (uint32_t)ld32(second ? sr : xr, (M + p) * 4);
+        uint32_t *t = (second ? ts : tx) + c * 5 * M2 + o;
+        t[0] = lo;
+        t[M2] = lo ^ hi;
+        t[2 * M2] = hi;
+        t[3 * M2] = lo;
+        t[4 * M2] = lo ^ hi;
+        t += NA * 5 * M2;
+        t[0] = lo ^ hi;
+        t[M2] = lo;
+        t[2 * M2] = hi;
+        t[3 * M2] = lo ^ hi;
+        t[4 * M2] = lo;
+    }
+    for (int i = tid; i < NP * G::va; i += NTH) va[i] = 0;
+    __syncthreads();
+    // values at the points u^(3 i + r): sums of coefficients rotated by
+    // (3 i + r) c U
+    for (int tk = tid; tk < 2 * NP * M2; tk += NTH) {
+        const bool second = tk >= NP * M2;
+        const int k = second ? tk - NP * M2 : tk;
+        const int pt = k / M2, p0 = k - pt * M2;
+        const int r = pt >= NA ? 2 : 1, step = U * (3 * (pt - (r - 1) * NA) + r);
+        const uint32_t *t = (second ? ts : tx) + (r - 1) * NA * 5 * M2;
+        uint32_t b0 = 0, b1 = 0;
+        int qq = p0;
+#pragma unroll
+        for (int c = 0; c < NA; ++c) {
+            b0 ^= t[c * 5 * M2 + qq];
+            b1 ^= t[c * 5 * M2 + qq + 2 * M2];
+            qq -= step;
+            if (qq < 0) qq += 3 * M2;
+        }
+        if (second) {
+            uint32_t *o = vb + pt * G::vb + p0;
+            o[0] = b0;
+            o[M2] = b0 ^ b1;
+            o[2 * M2] = b1;
+            o[3 * M2] = b0;
+        } else {  // bit-reversed as a whole, after one word of zeros
+            uint32_t *o = va + pt * G::va;
+            o[2 * M2 - p0] = __builtin_bitreverse32(b0);
+            o[M2 - p0] = __builtin_bitreverse32(b1);
+        }
+    }
+    __syncthreads();
+    // leaf products.  out[x] = sum_k row[x + k] col[k - q - 1] over the row
+    // operand's bits and the reversed column operand: as in the direct form,
+    // with the row windows (multiples of 16 bits) expanded once into LDS.
+    {
+        uint32_t *ex = ts + wave * G::units * 4;
+        const int q = lane & 15, kb = lane >> 4;
+        for (int pt = wave; pt < NP; pt += G::waves) {
+            const uint32_t *row = vb + pt * G::vb;
+            for (int u = lane; u < 8 * M2; u += 64) {
+                const uint32_t w = funnel(row[(u >> 1) + 1], row[u >> 1], 16u * (uint32_t)(u & 1));
+                *(gf_v4i *)(ex + u * 4) = expand_a(w);
+            }
+            __builtin_amdgcn_wave_barrier();
+            const uint32_t *col = va + pt * G::va + kb;
+            const uint32_t *rowx = ex + (q + 2 * kb) * 4;
+#pragma unroll 1
+            for (int sw = 0; sw < G::sweeps; ++sw) {
+                constexpr int NT = G::nt, ST = G::steps;
+                const uint32_t *rx = rowx + sw * NT * 64;
+                gf_v4f acc[NT] = {};
+                gf_v4i af[ST + 2 * NT - 2];
+#pragma unroll
+                for (int k = 0; k < ST; ++k) {
+                    const gf_v4i b = expand_b(funnel(col[4 * k + 1], col[4 * k], (uint32_t)(31 - q)));
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        // fragment k + 2 t, read at its first use
+                        if (k < 2 || t == NT - 1) af[k + 2 * t] = *(const gf_v4i *)(rx + (k + 2 * t) * 32);
+                        acc[t] = bit_mfma(af[k + 2 * t], b, acc[t]);
+                    }
+                }
+                // out words 0 .. M2 - 1 are the high half, then the low half
+                uint32_t w0 = 0;
+                static_for_up<0, NT>([&](auto t) PA_INLINE { w0 = tile_words<8 * t>(acc[t], w0); });
+                uint32_t *o = tx + pt * 5 * M2;
+                auto put = [&](int x, uint32_t v) PA_INLINE {
+                    if (x < M2) {
+                        o[2 * M2 + x] = v;
+                    } else if (x < 2 * M2) {
+                        o[x - M2] = v;
+                        o[x + 2 * M2] = v;
+                    }
+                };
+                if (lane < 8 * NT) put(sw * NT * 8 + lane, w0);
+            }
+            __builtin_amdgcn_wave_barrier();
+            for (int x = lane; x < M2; x += 64) {
+                uint32_t *o = tx + pt * 5 * M2 + x;
+                const uint32_t v = o[0] ^ o[2 * M2];
+                o[M2] = v;
+                o[4 * M2] = v;
+            }
+        }
+    }
+    __syncthreads();
+    // inverse: coefficient c modulo z^NA - v^(r M2)
+    for (int tk = tid; tk < 2 * M; tk += NTH) {
+        const int r = tk >= M ? 2 : 1, k = tk - (r - 1) * M;
+        const int c = k / M2, p0 = k - c * M2;
+        const uint32_t *t = tx + (r - 1) * NA * 5 * M2;
+        uint32_t b0 = 0, b1 = 0;
+        const int step = (3 * U * c) % (3 * M2);
+        int qq = p0 + U * r * c;
+        if (qq >= 3 * M2) qq -= 3 * M2;
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            b0 ^= t[i * 5 * M2 + qq];
+            b1 ^= t[i * 5 * M2 + qq + 2 * M2];
+            qq += step;
+            if (qq >= 3 * M2) qq -= 3 * M2;
+        }
+        va[tk] = b0;          // [r][c][p0], low halves, then high halves
+        va[2 * M + tk] = b1;
+    }
+    __syncthreads();
+    // the coefficients C_c (2 M2 words each) overlap by M2: block b of the
+    // product is C_b low + C_(b-1) high, and v^(2M) = v^M + 1
+    {
+        const uint32_t *l1 = va, *l2 = va + M, *h1 = va + 2 * M, *h2 = va + 3 * M;
+        auto lo_of = [&](int c, int o) PA_INLINE { return l1[c * M2 + o] ^ h1[c * M2 + o] ^ h2[c * M2 + o]; };
+        auto hi_of = [&](int c, int o) PA_INLINE { return l1[c * M2 + o] ^ l2[c * M2 + o] ^ h2[c * M2 + o]; };
+        auto lo2_of = [&](int c, int o) PA_INLINE { return l1[c * M2 + o] ^ l2[c * M2 + o]; };
+        auto hi2_of = [&](int c, int o) PA_INLINE { return h1[c * M2 + o] ^ h2[c * M2 + o]; };
+        for (int p = tid; p < M; p += NTH) {
+            const int c = p / M2, o = p - c * M2;
+            uint32_t c0 = lo_of(c, o), c1 = lo2_of(c, o);
+            if (c > 0) {
+                c0 ^= hi_of(c - 1, o);
+                c1 ^= hi2_of(c - 1, o);
+            } else {
+                const uint32_t top = hi2_of(NA - 1, o);
+                c0 ^= top;
+                c1 ^= hi_of(NA - 1, o) ^ top;
+            }
+            vb[p] = c0;
+            vb[M + p] = c0 ^ c1;
+            vb[2 * M + p] = c1;
+        }
+    }
+    __syncthreads();
+    // with the overlap of the chunk before: beta[p] + beta[p + 2M - g tau]
+    {
+        const rsrc_t ho = make_rsrc(job.A + (size_t)T * 2 * M + (size_t)tau * 3 * M, 3 * M * 4);
+        const int d = (2 * M + 3 * M - (g * tau) % (3 * M)) % (3 * M);
+        for (int p = tid; p < 3 * M; p += NTH) {
+            int k = p + d;
+            if (k >= 3 * M) k -= 3 * M;
+            st32(ho, p * 4, (int)(vb[p] ^ vb[k]));
+        }
+    }
+}
+
+// P3: output word G = t M + e is the sum over tau of word e + g t tau
+// (modulo 3 M) of product tau.  A workgroup computes 64 words; its waves
+// share tau.  Grid: (ceil(words / 64), jobs).
+template <int T>
+__global__ void __launch_bounds__(64 * kGfWaves) k_gf_inv(JobArgs ja, int g) {
+    static_assert(T % kGfWaves == 0, "waves share tau evenly");
+    constexpr int K = T / kGfWaves;
+    const JobDesc job = job_of(ja, uni(blockIdx.y));
+    const int M = T / 3 * g, M3 = 3 * M;
+    const uint32_t words = (job.m + 63u) / 64u * 2u;
+    if (blockIdx.x * 64u >= words) return;
+    const int lane = threadIdx.x & 63, wave = (int)uni(threadIdx.x >> 6);
+    const uint32_t w = blockIdx.x * 64u + (uint32_t)lane, G = job.off0 / 32u + w;
+    const int t = (int)(G / (uint32_t)M), e = (int)(G - (uint32_t)t * (uint32_t)M);
+    const rsrc_t h = make_rsrc(job.A + (size_t)T * 2 * M, (uint32_t)(T * M3 * 4));
+    const int tm = t % T;  // (past the last chunk: only for words past the output)
+    int p = e + g * ((tm * (wave * K)) % T);
+    if (p >= M3) p -= M3;
+    const int step = g * tm;
+    uint32_t acc = 0;
+    const int base = wave * K * M3 * 4;
+#pragma unroll 27
+    for (int k = 0; k < K; ++k) {
+        acc ^= (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(h, p * 4, base + k * M3 * 4, 0);
+        p += step;
+        if (p >= M3) p -= M3;
+    }
+    __shared__ uint32_t red[kGfWaves][64];
+    red[wave][lane] = acc;
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+        for (int i = 1; i < kGfWaves; ++i) acc ^= red[i][lane];
+        if (w < words) OutWords(job).put(w, acc);
+    }
+}
+
+// ---------------------------------------------------------------- launchers
+
+static hipError_t set_lds_limits(int *limit);  // once per device, with gf_set_lds_limits
+
+static hipError_t gf_launch(const void *fn, dim3 grid, int threads, void **args, size_t lds, hipStream_t s,
+                            hipEvent_t e0, hipEvent_t e1) {
+    if (!fn || grid.x == 0 || grid.y == 0 || grid.z == 0 || grid.y > 65535 || grid.z > 65535)
+        return hipErrorInvalidConfiguration;
+    int limit = 0;
+    const hipError_t e = set_lds_limits(&limit);
+    if (e != hipSuccess) return e;
+    if (lds > (size_t)limit) return hipErrorInvalidConfiguration;
+    return hipExtLaunchKernel(fn, grid, dim3((unsigned)threads), args, lds, s, e0, e1, 0);
+}
+
+hipError_t launch_gf_direct(const GfChoice &c, const JobArgs &ja, int njobs, hipStream_t s, hipEvent_t e0,
+                            hipEvent_t e1) {
+    const void *fn = nullptr;
+    const bool parts = c.slices > 1;
+    if (c.nt == 4) fn = parts ? (const void *)k_gf_direct<4, true> : (const void *)k_gf_direct<4, false>;
+    if (c.nt == 8) fn = parts ? (const void *)k_gf_direct<8, true> : (const void *)k_gf_direct<8, false>;
+    if (c.form != kGfDirect || ja.seg || c.slices < 1) return hipErrorInvalidConfiguration;
+    void *args[] = {(void *)&ja};
+    const uint32_t per = 256u * (uint32_t)c.nt;
+    return gf_launch(fn, dim3((c.max_m + per - 1) / per, (unsigned)c.slices, (unsigned)njobs), 512, args, 0, s, e0, e1);
+}
+
+hipError_t launch_gf_parts(const GfChoice &c, const JobArgs &ja, int njobs, hipStream_t s, hipEvent_t e0,
+                           hipEvent_t e1) {
+    if (c.form != kGfDirect || ja.seg) return hipErrorInvalidConfiguration;
+    int slices = c.slices;
+    void *args[] = {(void *)&ja, (void *)&slices};
+    const uint32_t words = (c.max_m + 255) / 256 * 8;
+    return gf_launch((const void *)k_gf_parts, dim3((words + 255) / 256, (unsigned)njobs), 256, args, 0, s, e0, e1);
+}
+
+hipError_t launch_gf_fwd(const GfChoice &c, int nsrc, const JobArgs &ja, int njobs, hipStream_t s, hipEvent_t e0,
+                         hipEvent_t e1) {
+    const void *fn = nullptr;
+    int P = 9, Q = 27;
+    if (c.T == 81) fn = (const void *)k_gf_fwd<9, 9>, Q = 9;
+    if (c.T == 243) fn = (const void *)k_gf_fwd<27, 9>;
+    if (c.T == 729) fn = (const void *)k_gf_fwd<27, 27>, P = 27;
+    if (c.form != kGfSplit || ja.seg || c.F < 1 || (c.g * P) % c.F) return hipErrorInvalidConfiguration;
+    int g = c.g, F = c.F;
+    void *args[] = {(void *)&ja, (void *)&g, (void *)&F};
+    return gf_launch(fn, dim3((unsigned)(Q * (g * P / F)), (unsigned)nsrc, (unsigned)njobs), 64 * kGfWaves, args,
+                     (size_t)P * (5 * Q / 3) * F * 4, s, e0, e1);
+}
+
+// The product kernels that exist: (a, M2) and their LDS.
+struct GfMulFn {
+    int a, M2;
+    const void *fn;
+    int threads;
+    size_t lds;
+};
+template <int A, int M2>
+static GfMulFn gf_mul_fn() {
+    using G = GfMul<A, M2>;
+    static_assert(G::lds_words * 4 <= 160 * 1024, "a workgroup's LDS");
+    return {A, M2, (const void *)k_gf_mul<A, M2>, 64 * G::waves, (size_t)G::lds_words * 4};
+}
+static const GfMulFn *gf_mul_table(int *count) {
+    static const GfMulFn table[] = {gf_mul_fn<1, 9>(),  gf_mul_fn<1, 18>(), gf_mul_fn<1, 27>(),
+                                    gf_mul_fn<2, 9>(),  gf_mul_fn<2, 18>(), gf_mul_fn<2, 27>(),
+                                    gf_mul_fn<2, 36>(), gf_mul_fn<2, 45>(), gf_mul_fn<3, 27>()};
+    *count = (int)(sizeof(table) / sizeof(table[0]));
+    return table;
+}
+
+// Kernels whose workgroups use more than the default LDS.
+static hipError_t gf_set_lds_limits(int maxb) {
+    int n = 0;
+    const GfMulFn *t = gf_mul_table(&n);
+    hipError_t e = hipSuccess;
+    for (int i = 0; i < n && e == hipSuccess; ++i)
+        e = hipFuncSetAttribute(t[i].fn, hipFuncAttributeMaxDynamicSharedMemorySize, maxb);
+    for (const void *f : {(const void *)k_gf_fwd<9, 9>, (const void *)k_gf_fwd<27, 9>, (const void *)k_gf_fwd<27, 27>})
+        if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, maxb);
+    return e;
+}
+
+hipError_t launch_gf_mul(const GfChoice &c, bool resident, const JobArgs &ja, int njobs, hipStream_t s, hipEvent_t e0,
+                         hipEvent_t e1) {
+    if (c.form != kGfSplit || ja.seg) return hipErrorInvalidConfiguration;
+    int n = 0, T = c.T, g = c.g, r = resident ? 1 : 0;
+    const GfMulFn *t = gf_mul_table(&n);
+    void *args[] = {(void *)&ja, (void *)&T, (void *)&g, (void *)&r};
+    for (int i = 0; i < n; ++i)
+        if (t[i].a == c.a && t[i].M2 == c.M2)
+            return gf_launch(t[i].fn, dim3((unsigned)T, (unsigned)njobs), t[i].threads, args, t[i].lds, s, e0, e1);
+    return hipErrorInvalidConfiguration;
+}
+
+hipError_t launch_gf_inv(const GfChoice &c, const JobArgs &ja, int njobs, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    const void *fn = nullptr;
+    if (c.T == 81) fn = (const void *)k_gf_inv<81>;
+    if (c.T == 243) fn = (const void *)k_gf_inv<243>;
+    if (c.T == 729) fn = (const void *)k_gf_inv<729>;
+    if (c.form != kGfSplit || ja.seg) return hipErrorInvalidConfiguration;
+    int g = c.g;
+    void *args[] = {(void *)&ja, (void *)&g};
+    const uint32_t words = (c.max_m + 63) / 64 * 2;
+    return gf_launch(fn, dim3((words + 63) / 64, (unsigned)njobs), 64 * kGfWaves, args, 0, s, e0, e1);
+}
+
+}  // namespace pa

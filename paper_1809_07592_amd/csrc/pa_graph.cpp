@@ -28,6 +28,7 @@ struct pa_graph_s {
     // group layouts the launches were captured for (length, plain-path
     // blocks, blocks per shared seed)
     std::vector<std::vector<uint64_t>> groups;
+    std::vector<pa::GfChoice> forms;  // per group: the form captured
 };
 
 namespace {
@@ -59,13 +60,16 @@ pa_status pa_graph_create(const pa_block *blocks, uint32_t count, int modified, 
     *graph = nullptr;
     if (count == 0) return fail(PA_ERR_INVALID_ARG, "empty block array");
     BatchPrep bp;
-    PA_TRY(prepare_batch(blocks, count, modified != 0, &bp, batch_form(kFormLanes)));
+    PA_TRY(prepare_batch(blocks, count, modified != 0, &bp, batch_form(kFormLanes), true));
     pa_graph_s *g = new (std::nothrow) pa_graph_s();
     if (!g) return fail(PA_ERR_OUT_OF_MEMORY, "host allocation");
     g->count = count;
     g->modified = modified != 0;
     g->form = bp.form;
-    for (const auto &gr : bp.groups) g->groups.push_back(gr.layout());
+    for (const auto &gr : bp.groups) {
+        g->groups.push_back(gr.layout());
+        g->forms.push_back(gr.plan.gf);
+    }
     auto bail = [&](pa_status st) {
         destroy_graph(g);
         return st;
@@ -126,14 +130,16 @@ pa_status pa_graph_update(pa_graph_t graph, const pa_block *blocks, uint32_t cou
     if (dev != graph->device) return fail(PA_ERR_INVALID_ARG, "graph belongs to another device");
     if (count != graph->count) return fail(PA_ERR_INVALID_ARG, "block count differs from the graph's");
     BatchPrep bp;
-    PA_TRY(prepare_batch(blocks, count, graph->modified, &bp, graph->form));
+    PA_TRY(prepare_batch(blocks, count, graph->modified, &bp, graph->form, true));
     bool same = bp.groups.size() == graph->groups.size();
     for (size_t i = 0; same && i < bp.groups.size(); ++i) same = bp.groups[i].layout() == graph->groups[i];
     if (!same)
         return fail(PA_ERR_INVALID_ARG,
                     "blocks need other transform lengths, or share seeds otherwise, than the graph was built for");
-    // Same group layouts give the same table layout (descriptors, residues
-    // and spectra in group order); the captured launches keep their plans.
+    // Same group layouts give the same table layout (descriptors, areas and
+    // spectra in group order); the captured launches keep their plans and
+    // forms.
+    for (size_t i = 0; i < bp.groups.size(); ++i) bp.groups[i].plan.gf = graph->forms[i];
     build_table(bp, graph->buf);
     return stage_upload((hipStream_t)stream, graph->buf, bp.blob.data(), bp.blob.size());
 }

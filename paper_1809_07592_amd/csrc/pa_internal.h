@@ -194,6 +194,7 @@ struct LenPlan {
     XDesc row;               // length-C transform (row pass)
     const double2 *twist_lo; // omega_L^i, i < 4096
     const double2 *twist_hi; // omega_L^(4096 i), i < ceil(L / 4096)
+    int default_geometry;    // 1: the library's own choice for L
     const double2 *alpha_i;  // [k1][u] = omega_L^(-k1 * (C/rho0) * u) / L (inverse twist of the row pass)
 };
 

@@ -1287,6 +1287,12 @@ __global__ void __launch_bounds__(512) k_colinv(const LenPlan *__restrict__ plan
     col_round<MODE_INV, true, false, MAXLG, false, CS>(xd, ftw, itw, first_round, wsh, pre, load_lds, mid, store_bits);
 }
 
+}  // namespace pa
+
+#include "pa_gf2_kernels.h"
+
+namespace pa {
+
 // ----------------------------------------------------------------- launchers
 
 // The row kernel for first-round kind fk and fixed shape sh (0: general).
@@ -1395,6 +1401,8 @@ static hipError_t set_lds_limits(int *limit) {
                 e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, maxb);
                 if (e != hipSuccess) return e;
             }
+        e = gf_set_lds_limits(maxb);
+        if (e != hipSuccess) return e;
         g_lds_limit[dev] = maxb;
     }
     *limit = g_lds_limit[dev];

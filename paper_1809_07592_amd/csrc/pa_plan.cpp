@@ -338,6 +338,47 @@ void plan_geometry(uint64_t L, const Geometry &g, LenPlan &lp, XTables *ct, XTab
     if (lp.row.round[0].kind >= 8 || lp.row.round[0].kind == 3) throw std::runtime_error("no row kernel for this first round");
 }
 
+// ------------------------------------------------------- carry-less forms
+
+GfChoice gf_split_for(uint64_t bits, uint64_t words) {
+    // ascending capacity 32 T M: T, g, a, M2 = M / 3^a, F (divides g P)
+    static const struct {
+        int T, g, a, F;
+    } sizes[] = {{81, 1, 1, 9},   {81, 2, 1, 18},  {81, 3, 1, 27},  {243, 1, 2, 9},  {243, 2, 2, 18}, {243, 3, 2, 27},
+                 {243, 4, 2, 18}, {243, 5, 2, 15}, {729, 1, 2, 27}, {729, 3, 3, 27}};
+    for (const auto &z : sizes) {
+        GfChoice c;
+        c.form = kGfSplit;
+        c.T = z.T;
+        c.g = z.g;
+        c.a = z.a;
+        c.F = z.F;
+        c.M2 = c.chunk_words() / (z.a == 1 ? 3 : z.a == 2 ? 9 : 27);
+        if (c.cyclic_bits() >= bits && c.work_words() <= words) return c;
+    }
+    return GfChoice{};
+}
+
+GfChoice gf_plain_for(uint64_t n, uint64_t m, uint64_t bits, uint64_t words, int njobs) {
+    const double products = (double)n * (double)m;
+    GfChoice c;
+    if (products <= (njobs == 1 ? 1.0e10 : 2.0e9)) {
+        c.form = kGfDirect;
+        c.nt = 4;
+        c.max_m = (uint32_t)m;
+        const uint64_t groups = (m + 1023) / 1024 * (uint64_t)njobs, units = (n + 15 + 1023) / 1024;
+        c.slices = 1;
+        if (units > 64) {
+            c.slices = (int)std::max<uint64_t>(1, std::min<uint64_t>(512 / std::max<uint64_t>(groups, 1), units / 16));
+            if (gf_direct_words(c) > words) c.slices = 1;
+        }
+        return c;
+    }
+    c = gf_split_for(bits, words);
+    c.max_m = (uint32_t)m;
+    return c;
+}
+
 Geometry geometry_of(const LenPlan &lp) {
     return Geometry{lp.log2R, lp.W, lp.row_first, lp.row_threads_fixed ? lp.row_threads : 0};
 }
@@ -389,7 +430,7 @@ bool find_len_plan(uint64_t L, const Geometry &g, PlanRef *out) {
     std::lock_guard<std::mutex> lk(g_mu);
     auto it = g_plans.find({dev, L, geometry_of(lp)});
     if (it == g_plans.end()) return false;
-    *out = {&it->second->plan, it->second->dplan};
+    *out = PlanRef{&it->second->plan, it->second->dplan, {}};
     return true;
 }
 
@@ -406,12 +447,17 @@ PlanRef get_len_plan(uint64_t L, const Geometry &geo) {
     const auto key = std::make_tuple(dev, L, eff);
     std::lock_guard<std::mutex> lk(g_mu);
     auto it = g_plans.find(key);
-    if (it != g_plans.end()) return {&it->second->plan, it->second->dplan};
+    if (it != g_plans.end()) return PlanRef{&it->second->plan, it->second->dplan, {}};
 
     auto e = std::make_unique<PlanEntry>();
     LenPlan &lp = e->plan;
     XTables ct, rt;
     plan_geometry(L, eff, lp, &ct, &rt);
+    {
+        LenPlan def;
+        plan_geometry(L, Geometry{}, def);
+        lp.default_geometry = eff == geometry_of(def) ? 1 : 0;
+    }
     lp.col.fwd_tw = upload(e->tables, ct.fwd);
     lp.col.inv_tw = upload(e->tables, ct.inv);
     lp.row.fwd_tw = upload(e->tables, rt.fwd);
@@ -451,7 +497,7 @@ PlanRef get_len_plan(uint64_t L, const Geometry &geo) {
               "plan L=%llu on device %d: R=%d C=%d W=%d, first row round %d, row workgroup %d%s, column LDS %d B",
               (unsigned long long)L, dev, lp.R, lp.C, lp.W, lp.rho0, lp.row_threads,
               lp.row_threads_fixed ? " (tuned)" : "", lp.col_lds * 4);
-    PlanRef out{&e->plan, e->dplan};
+    PlanRef out{&e->plan, e->dplan, {}};
     g_plans[key] = std::move(e);
     return out;
 }

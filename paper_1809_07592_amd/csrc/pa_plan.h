@@ -5,6 +5,7 @@
 
 #include <vector>
 
+#include "pa_gf2.h"
 #include "pa_internal.h"
 
 namespace pa {
@@ -49,11 +50,19 @@ inline void plan_geometry(uint64_t L, int log2R, int W, LenPlan &lp) { plan_geom
 // The effective geometry of a plan (defaults resolved).
 Geometry geometry_of(const LenPlan &lp);
 
-// A plan: host copy (for launch geometry) and the device copy the kernels read.
+// A plan: host copy (for launch geometry) and the device copy the kernels
+// read, and the form its launches take: the plan's transform (gf.form none)
+// or a carry-less form, which needs no tables.
 struct PlanRef {
-    const LenPlan *host;
-    const LenPlan *dev;
+    const LenPlan *host = nullptr;
+    const LenPlan *dev = nullptr;
+    GfChoice gf{};
 };
+
+// Whether launches of this plan may take a carry-less form: its geometry is
+// the default one.  A geometry set by the caller (or read from a tuning
+// file) selects the transform it describes.
+inline bool gf_allowed(const PlanRef &p) { return p.host->default_geometry != 0; }
 
 // Cached per-device plan for length L in geometry g.  Throws
 // std::bad_alloc / std::runtime_error on failure.

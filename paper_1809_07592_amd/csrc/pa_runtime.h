@@ -135,6 +135,7 @@ struct BatchPrep {
         double bytes = 0, ops = 0;      // algorithmic, for the profiler
     };
     bool modified = false;
+    bool any_sizes = false;  // launches must serve any blocks of these lengths
     BatchForm form = kFormFlat;
     std::vector<pa_block> blocks;
     std::vector<uint64_t> block_len;
@@ -151,8 +152,13 @@ struct BatchPrep {
 // job lookup in every workgroup and no overlap between lengths), on a
 // uniform and on an uneven batch.
 BatchForm batch_form(BatchForm dflt);
+// any_sizes: a captured graph's launches, which later blocks of the same
+// lengths must fit.
 pa_status prepare_batch(const pa_block *blocks, uint32_t count, bool modified, BatchPrep *bp,
-                        BatchForm form);
+                        BatchForm form, bool any_sizes = false);
+// Words of the areas A and S that a block needs in the plan's form.
+uint64_t area_words_a(const PlanRef &p);
+uint64_t area_words_s(const PlanRef &p);
 // Fills bp.blob (the table region) for workspace `ws` (which must hold
 // bp.total_bytes).
 void build_table(BatchPrep &bp, void *ws);

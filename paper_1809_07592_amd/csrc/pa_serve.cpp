@@ -278,6 +278,9 @@ pa_status pa_server_s::build_spectrum(Spectrum *sp) {
     }
     pa::PlanRef p{};
     PA_TRY(plan_for(sp->L, 1, &p));
+    // requests of this length end within L; seed bits past the cyclic length
+    // would wrap onto outputs.  Areas are 4 L bytes in every form.
+    if (gf_allowed(p)) p.gf = pa::gf_split_for(std::min(sp->L, sp->bits_len + 126), sp->L);
     sp->plan = p;
     PA_TRY(run_seed_path(p, sp->bits, std::min(sp->bits_len, sp->L), sp->S, plan_stream));
     hipError_t e = take_event(&sp->ready);
@@ -316,7 +319,8 @@ pa_status pa_server_s::launch(std::vector<Req *> &rs, Batch *b) {
     for (Req *r : rs) order.push_back({r, r->spec});
     std::sort(order.begin(), order.end(), [](const auto &a, const auto &c) {
         if (a.first->L != c.first->L) return a.first->L < c.first->L;
-        return a.second->plan.host < c.second->plan.host;
+        if (a.second->plan.host != c.second->plan.host) return a.second->plan.host < c.second->plan.host;
+        return a.second->plan.gf.cyclic_bits() < c.second->plan.gf.cyclic_bits();
     });
     for (auto &o : order) {
         Req *r = o.first;
@@ -324,9 +328,12 @@ pa_status pa_server_s::launch(std::vector<Req *> &rs, Batch *b) {
         pa::JobDesc j = plain_job(r->key, r->n, nullptr, r->m, r->out, A, nullptr);
         j.Shat = o.second->S;
         table.push_back(j);
-        if (groups.empty() || groups.back().plan.host != o.second->plan.host)
+        if (groups.empty() || groups.back().plan.host != o.second->plan.host ||
+            groups.back().plan.gf.cyclic_bits() != o.second->plan.gf.cyclic_bits())
             groups.push_back({o.second->plan, 0, {}});
         groups.back().count++;
+        pa::GfChoice &gf = groups.back().plan.gf;
+        gf.max_m = std::max(gf.max_m, (uint32_t)r->m);
         groups.back().reqs.push_back(r);
     }
     if (table.size() > sc.cap) return fail(PA_ERR_DEVICE, "job table overflow");
