@@ -31,8 +31,8 @@ struct GfChoice {
     // direct: tiles of 256 outputs per workgroup, slices of the key
     int nt = 0, slices = 0;
     // split: T = 3^k chunks, word unit g, log3 of the half point count a,
-    // leaf half length M2 (words), classes of the forward pass per workgroup
-    int T = 0, g = 0, a = 0, M2 = 0, F = 0;
+    // leaf half length M2 (words)
+    int T = 0, g = 0, a = 0, M2 = 0;
     // largest output length (bits) of the launch's jobs: the grid's extent
     uint32_t max_m = 0;
     int chunk_words() const { return T / 3 * g; }                             // M

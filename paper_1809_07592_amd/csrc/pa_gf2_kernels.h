@@ -15,13 +15,14 @@ __device__ __forceinline__ uint32_t funnel(uint32_t hi, uint32_t lo, uint32_t sh
     return __builtin_amdgcn_alignbit(hi, lo, sh);
 }
 
-// The word after byte offset o, which may be negative: the sum is formed in
-// the register, since a hardware offset added to a negative one is out of
-// range.
-__device__ __forceinline__ uint32_t ld32_next(rsrc_t r, int o) {
-    int k = o + 4;
-    asm("" : "+v"(k));
-    return (uint32_t)ld32(r, k);
+// Load at a byte offset that may be negative (out of range: 0).  The offset
+// is made opaque: the compiler would otherwise form it as a register, which
+// can be negative for a neighbouring load of the same code, plus a positive
+// instruction offset, and a negative register is out of range whatever is
+// added to it.
+__device__ __forceinline__ uint32_t ld32_any(rsrc_t r, int o) {
+    asm("" : "+v"(o));
+    return (uint32_t)ld32(r, o);
 }
 
 // One 16 x 16 x 128 binary product on the matrix cores: the operands hold
@@ -124,11 +125,13 @@ __global__ void __launch_bounds__(512) k_gf_direct(JobArgs ja) {
     };
     auto fetch_b = [&](int k, bool edge) PA_INLINE {
         const int w = bw - 4 * k;
-        uint32_t lo = (uint32_t)ld32(xb, w * 4), hi;
-        if (!edge) {
+        uint32_t lo, hi;
+        if (!edge) {  // (uniform)
+            lo = (uint32_t)ld32(xb, w * 4);
             hi = (uint32_t)ld32(xb, w * 4 + 4);
-        } else {  // uniform: the key's first and last words
-            hi = ld32_next(xb, w * 4);
+        } else {  // windows across the key's first or last word, or past them
+            lo = ld32_any(xb, w * 4);
+            hi = ld32_any(xb, w * 4 + 4);
             if (w == 0) lo &= first_mask;
             if (w == last) lo &= last_mask;
             if (w + 1 == 0) hi &= first_mask;
@@ -210,125 +213,123 @@ __global__ void __launch_bounds__(256) k_gf_parts(JobArgs ja, int slices) {
 // thirds determine the element; a table of five thirds (one period and two
 // more) gives lo and hi of a rotation at a linear index.
 
-// Word W of a bit string taken from bit `off` of base (may be negative: the
-// bits before are zeros), bits outside [lo, hi) of the result cleared.
-struct BitSource {
-    rsrc_t buf;
-    int dw;         // word of bit 0
-    uint32_t rem;   // bit position inside it
-    int lo, hi;     // valid bits
-    __device__ __forceinline__ uint32_t word(int W, bool edge) const {
-        const int i = (W + dw) * 4;
-        uint32_t v = (uint32_t)ld32(buf, i);
-        if (rem) v = funnel(edge ? ld32_next(buf, i) : (uint32_t)ld32(buf, i + 4), v, rem);
-        if (edge) {
-            const int a = lo - 32 * W, b = hi - 32 * W;
-            const uint32_t ma = a <= 0 ? ~0u : a >= 32 ? 0u : ~0u << a;
-            const uint32_t mb = b >= 32 ? ~0u : b <= 0 ? 0u : (1u << b) - 1u;
-            v &= ma & mb;
-        }
-        return v;
-    }
-};
+// a - b (mod n) for 0 <= a, b < n as one subtraction, one addition and an
+// unsigned minimum.
+__device__ __forceinline__ uint32_t sub_mod(uint32_t a, uint32_t b, uint32_t n) {
+    const uint32_t d = a - b;
+    return min(d, d + n);
+}
+__device__ __forceinline__ uint32_t add_mod(uint32_t a, uint32_t b, uint32_t n) {
+    const uint32_t d = a + b;
+    return min(d, d - n);
+}
 
 // P1: forward transform of the chunks a_t (M words each, t < T = P Q) at
-// the T-th root v^g:  X_tau = sum_t v^(g tau t) a_t.  With tau = rho + Q
+// the T-th root v^G:  X_tau = sum_t v^(G tau t) a_t.  With tau = rho + Q
 // sigma and t = t0 + P t1 the inner sums over t1 are formed by scattering
 // every chunk, rotated, into tile t0, and a length-P transform over t0
-// follows.  Word positions split into classes modulo Cm = g P that no
+// follows.  Word positions split into classes modulo Cm = G P that no
 // rotation of the second step leaves; a workgroup takes one rho and F
-// classes (F divides Cm), so its tile is P x Q x F words.
+// classes (F divides Cm), so its tile is P x Q x F words.  What bounds it
+// is vector issue: a chunk word costs its load, three operations for its
+// target's address and an LDS exclusive or, and every word is read by Q
+// workgroups (from the caches).  Everything but rho is a constant, since
+// run-time divisions by the unit cost four times the rest.
 // Grid: (Q Cm / F, sources, jobs), 9 waves.  Wave w owns tiles t0 = w,
 // w + 9, ...: nothing else writes them before the barrier.
 constexpr int kGfWaves = 9;
 
-template <int Q, int P>
-__global__ void __launch_bounds__(64 * kGfWaves) k_gf_fwd(JobArgs ja, int g, int F) {
-    constexpr int T = P * Q, Q3 = Q / 3;
-    static_assert(P % kGfWaves == 0 && Q % 9 == 0, "tiles are dealt to 9 waves, rows unrolled by 9");
+template <int Q, int P, int G, int F>
+__global__ void __launch_bounds__(64 * kGfWaves) k_gf_fwd(JobArgs ja) {
+    constexpr int T = P * Q, Q3 = Q / 3, M = T / 3 * G, Cm = G * P, NF = Cm / F;
+    static_assert(P % kGfWaves == 0 && Q % 9 == 0 && Cm % F == 0, "tiles are dealt to 9 waves, rows unrolled by 9");
+    constexpr int third = Q3 * F, period = Q * F, trow = 5 * third;  // words of a tile: five thirds
     const bool src = blockIdx.y != 0;
     const JobDesc job = job_of(ja, uni(blockIdx.z));
-    const int M = T / 3 * g, Cm = g * P, nf = Cm / F;
-    const int rho = (int)blockIdx.x / nf, f0 = ((int)blockIdx.x - rho * nf) * F;
+    const int rho = (int)blockIdx.x / NF, f0 = ((int)blockIdx.x - rho * NF) * F;
     uint32_t *tile = (uint32_t *)pa_lds;  // [P][5 Q / 3][F]
-    const int trow = 5 * Q3 * F;
     const int lane = threadIdx.x & 63, wave = (int)uni(threadIdx.x >> 6);
 
-    BitSource in;
-    {
-        const uint64_t *base = src ? job.seed : job.key;
-        const int nbits = (int)(src ? job.seed_bits : job.n);
-        const int shift = src ? 0 : (int)job.shift, off = src ? 0 : (int)job.key_off;
-        // the string starts `shift` bits after position 0 and is read from
-        // bit `off` of the buffer
-        const int d = (off & 31) - shift;
-        const uint32_t *b32 = (const uint32_t *)base + (off >> 5);
-        in.buf = make_rsrc(b32, (uint32_t)(((off & 31) + nbits + 31) / 32 * 4));
-        in.dw = d >> 5;
-        in.rem = (uint32_t)d & 31u;
-        in.lo = shift;
-        in.hi = shift + nbits;
-    }
-    const int rows = min(T, (in.hi + 32 * M - 1) / (32 * M));  // chunks that hold bits
+    // word W of the source is bits [32 W, 32 W + 32) from bit `off` of the
+    // buffer, `rem` of its first word
+    const int nbits = (int)(src ? job.seed_bits : job.n);
+    const uint32_t off = src ? 0u : job.key_off, rem = off & 31u;
+    const rsrc_t in = make_rsrc((const uint32_t *)(src ? job.seed : job.key) + (off >> 5),
+                                ((rem + (uint32_t)nbits + 31) / 32 * 4));
+    const int last = (nbits - 1) >> 5;  // the last word, cut to its valid bits
+    const uint32_t last_mask = ~0u >> (31 - ((nbits - 1) & 31));
+    const int rows = last / M + 1;      // chunks that hold bits
 
-    const int lanes = Q3 * F;  // words of a chunk in the workgroup's classes
     for (int t0 = wave; t0 < P; t0 += kGfWaves) {
         uint32_t *tl = tile + t0 * trow;
-        for (int i = lane; i < Q * F; i += 64) tl[i] = 0;
-        const int s0 = (g * rho * t0) % (3 * M), sc = s0 % Cm, si = s0 / Cm;
-        for (int l = lane; l < lanes; l += 64) {
+        for (int i = lane; i < period; i += 64) tl[i] = 0;
+        const int s0 = G * ((rho * t0) % T), sc = s0 % Cm, si = s0 / Cm;
+        for (int l = lane; l < third; l += 64) {
             const int i1 = l / F, f = l - i1 * F;
             int c = f0 + f - sc;  // class of the source word
-            const int wrap = c < 0;
+            const int wrap = c < 0 ? 1 : 0;
             c += wrap ? Cm : 0;
-            const int e = c + Cm * i1;
-            int ip = i1 + wrap + si;  // row of the target
-            if (ip >= Q) ip -= Q;
-            uint32_t *dst = tl + f;
-            // t1 = 0 .. Q - 1 in groups whose loads are in flight together
-#pragma unroll 1
-            for (int b = 0; b < Q && t0 + P * b < rows; b += 9) {
-                uint32_t w[9];
+            const int e = c + Cm * i1;  // its word in the chunk
+            // target: row (i1 + wrap + si + rho t1) mod Q
+            uint32_t at = (uint32_t)((i1 + wrap + si) * F);
+            at = min(at, at - (uint32_t)period);
+            // t1 = 0 .. Q - 1: all loads in flight, then the exclusive ors
+            // (whole groups of nine past the source's end are skipped)
+            uint32_t w[Q];
 #pragma unroll
-                for (int k = 0; k < 9; ++k) {
-                    const int t = t0 + P * (b + k);
-                    w[k] = in.word(t * M + e, t == 0 || t >= rows - 1);
+            for (int b = 0; b < Q; b += 9)
+                if (t0 + P * b < rows) {
+#pragma unroll
+                    for (int k = b; k < b + 9; ++k)
+                        w[k] = __builtin_amdgcn_raw_buffer_load_b32(in, e * 4, (t0 + P * k) * (M * 4), 0);
+                    if (rem) {
+#pragma unroll
+                        for (int k = b; k < b + 9; ++k)
+                            w[k] = funnel(__builtin_amdgcn_raw_buffer_load_b32(in, e * 4 + 4, (t0 + P * k) * (M * 4), 0),
+                                          w[k], rem);
+                    }
                 }
 #pragma unroll
-                for (int k = 0; k < 9; ++k) {
-                    atomicXor(dst + ip * F, w[k]);
-                    ip += rho;
-                    if (ip >= Q) ip -= Q;
+            for (int b = 0; b < Q; b += 9)
+                if (t0 + P * b < rows) {
+#pragma unroll
+                    for (int k = b; k < b + 9; ++k) {
+                        const int t = t0 + P * k;
+                        if (t >= rows - 1) {  // uniform
+                            const int W = t * M + e;
+                            w[k] = W > last ? 0u : W == last ? w[k] & last_mask : w[k];
+                        }
+                        atomicXor(tl + f + at, w[k]);
+                        at = add_mod(at, (uint32_t)(rho * F), (uint32_t)period);
+                    }
                 }
-            }
         }
-        // rows to periodic form, five thirds
-        for (int l = lane; l < lanes; l += 64) {
-            const uint32_t a = tl[l], b = tl[l + Q3 * F], c = tl[l + 2 * Q3 * F];
+        // to periodic form, five thirds
+        for (int l = lane; l < third; l += 64) {
+            const uint32_t a = tl[l], b = tl[l + third], c = tl[l + 2 * third];
             tl[l] = a ^ c;
-            tl[l + Q3 * F] = a ^ b;
-            tl[l + 2 * Q3 * F] = b ^ c;
-            tl[l + 3 * Q3 * F] = a ^ c;
-            tl[l + 4 * Q3 * F] = a ^ b;
+            tl[l + third] = a ^ b;
+            tl[l + 2 * third] = b ^ c;
+            tl[l + 3 * third] = a ^ c;
+            tl[l + 4 * third] = a ^ b;
         }
     }
     __syncthreads();
     const rsrc_t xo = make_rsrc(src ? job.S : job.A, (uint32_t)(2 * T * M * 4));
-    for (int tk = threadIdx.x; tk < P * lanes; tk += 64 * kGfWaves) {
-        const int sg = tk / lanes, l = tk - sg * lanes;
+    for (int tk = threadIdx.x; tk < P * third; tk += 64 * kGfWaves) {
+        const int sg = tk / third, l = tk - sg * third;
         const int i = l / F, f = l - i * F;
-        const int step = Q / P * sg * F;
-        int j = i * F;
+        const uint32_t step = (uint32_t)(Q / P * sg * F);
+        uint32_t j = (uint32_t)(i * F);
         uint32_t lo = 0, hi = 0;
 #pragma unroll
         for (int t0 = 0; t0 < P; ++t0) {
             const uint32_t *tl = tile + t0 * trow + f + j;
             lo ^= tl[0];
-            hi ^= tl[2 * Q3 * F];
-            j -= step;
-            if (j < 0) j += Q * F;
+            hi ^= tl[2 * third];
+            j = sub_mod(j, step, (uint32_t)period);
         }
-        const int at = ((rho + Q * sg) * 2 * M + i * Cm + f0 + f) * 4;
+        const int at = ((rho + Q * sg) * (2 * M) + i * Cm + f0 + f) * 4;
         st32(xo, at, (int)lo);
         st32(xo, at + M * 4, (int)hi);
     }
@@ -540,9 +541,10 @@ __global__ void __launch_bounds__((64 * GfMul<A, M2>::waves)) k_gf_mul(JobArgs j
     }
 }
 
-// P3: output word G = t M + e is the sum over tau of word e + g t tau
-// (modulo 3 M) of product tau.  A workgroup computes 64 words; its waves
-// share tau.  Grid: (ceil(words / 64), jobs).
+// P3: word W = t M + e of the cyclic product is the sum over tau of word
+// e + g t tau (modulo 3 M) of product tau.  A workgroup forms 64 words, its
+// waves share tau; output words start at bit n - 1, so 64 words give 63
+// shifted ones.  Grid: (ceil(output words / 63), jobs).
 template <int T>
 __global__ void __launch_bounds__(64 * kGfWaves) k_gf_inv(JobArgs ja, int g) {
     static_assert(T % kGfWaves == 0, "waves share tau evenly");
@@ -550,30 +552,32 @@ __global__ void __launch_bounds__(64 * kGfWaves) k_gf_inv(JobArgs ja, int g) {
     const JobDesc job = job_of(ja, uni(blockIdx.y));
     const int M = T / 3 * g, M3 = 3 * M;
     const uint32_t words = (job.m + 63u) / 64u * 2u;
-    if (blockIdx.x * 64u >= words) return;
+    if (blockIdx.x * 63u >= words) return;
     const int lane = threadIdx.x & 63, wave = (int)uni(threadIdx.x >> 6);
-    const uint32_t w = blockIdx.x * 64u + (uint32_t)lane, G = job.off0 / 32u + w;
-    const int t = (int)(G / (uint32_t)M), e = (int)(G - (uint32_t)t * (uint32_t)M);
+    const uint32_t w = blockIdx.x * 63u + (uint32_t)lane, W = (job.n - 1u) / 32u + w;
+    const int t = (int)(W / (uint32_t)M), e = (int)(W - (uint32_t)t * (uint32_t)M);
     const rsrc_t h = make_rsrc(job.A + (size_t)T * 2 * M, (uint32_t)(T * M3 * 4));
     const int tm = t % T;  // (past the last chunk: only for words past the output)
-    int p = e + g * ((tm * (wave * K)) % T);
-    if (p >= M3) p -= M3;
-    const int step = g * tm;
+    uint32_t p = add_mod((uint32_t)e, (uint32_t)(g * ((tm * (wave * K)) % T)), (uint32_t)M3) * 4u;
+    const uint32_t step = (uint32_t)(g * tm) * 4u, period = (uint32_t)M3 * 4u;
     uint32_t acc = 0;
     const int base = wave * K * M3 * 4;
 #pragma unroll 27
     for (int k = 0; k < K; ++k) {
-        acc ^= (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(h, p * 4, base + k * M3 * 4, 0);
-        p += step;
-        if (p >= M3) p -= M3;
+        acc ^= (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(h, (int)p, base + k * M3 * 4, 0);
+        p = add_mod(p, step, period);
     }
     __shared__ uint32_t red[kGfWaves][64];
+    __shared__ uint32_t sum[65];
     red[wave][lane] = acc;
     __syncthreads();
     if (wave == 0) {
 #pragma unroll
         for (int i = 1; i < kGfWaves; ++i) acc ^= red[i][lane];
-        if (w < words) OutWords(job).put(w, acc);
+        sum[lane] = acc;
+        if (lane == 0) sum[64] = 0;
+        __builtin_amdgcn_wave_barrier();
+        if (lane < 63 && w < words) OutWords(job).put(w, funnel(sum[lane + 1], acc, (job.n - 1u) & 31u));
     }
 }
 
@@ -613,18 +617,43 @@ hipError_t launch_gf_parts(const GfChoice &c, const JobArgs &ja, int njobs, hipS
     return gf_launch((const void *)k_gf_parts, dim3((words + 255) / 256, (unsigned)njobs), 256, args, 0, s, e0, e1);
 }
 
+// The forward kernels that exist, by (T, g): the classes per workgroup of
+// launches over many jobs (the widest runs of words that fill the lanes) and
+// of a few jobs (more workgroups).
+struct GfFwdFn {
+    int T, g, F;
+    bool many;
+    const void *fn;
+    unsigned wgs;
+    size_t lds;
+};
+template <int Q, int P, int G, int F>
+static GfFwdFn gf_fwd_fn(bool many) {
+    return {P * Q, G, F, many, (const void *)k_gf_fwd<Q, P, G, F>, (unsigned)(Q * (G * P / F)),
+            (size_t)P * (5 * Q / 3) * F * 4};
+}
+static const GfFwdFn *gf_fwd_table(int *count) {
+    static const GfFwdFn table[] = {
+        gf_fwd_fn<9, 9, 1, 9>(true),      gf_fwd_fn<9, 9, 2, 18>(true),   gf_fwd_fn<9, 9, 3, 27>(true),
+        gf_fwd_fn<27, 9, 1, 9>(true),     gf_fwd_fn<27, 9, 2, 18>(true),  gf_fwd_fn<27, 9, 3, 27>(true),
+        gf_fwd_fn<27, 9, 4, 18>(true),    gf_fwd_fn<27, 9, 5, 15>(true),  gf_fwd_fn<27, 27, 1, 9>(true),
+        gf_fwd_fn<27, 27, 3, 9>(true),    gf_fwd_fn<27, 9, 2, 6>(false),  gf_fwd_fn<27, 9, 3, 9>(false),
+        gf_fwd_fn<27, 9, 4, 6>(false),    gf_fwd_fn<27, 9, 5, 5>(false)};
+    *count = (int)(sizeof(table) / sizeof(table[0]));
+    return table;
+}
+
 hipError_t launch_gf_fwd(const GfChoice &c, int nsrc, const JobArgs &ja, int njobs, hipStream_t s, hipEvent_t e0,
                          hipEvent_t e1) {
-    const void *fn = nullptr;
-    int P = 9, Q = 27;
-    if (c.T == 81) fn = (const void *)k_gf_fwd<9, 9>, Q = 9;
-    if (c.T == 243) fn = (const void *)k_gf_fwd<27, 9>;
-    if (c.T == 729) fn = (const void *)k_gf_fwd<27, 27>, P = 27;
-    if (c.form != kGfSplit || ja.seg || c.F < 1 || (c.g * P) % c.F) return hipErrorInvalidConfiguration;
-    int g = c.g, F = c.F;
-    void *args[] = {(void *)&ja, (void *)&g, (void *)&F};
-    return gf_launch(fn, dim3((unsigned)(Q * (g * P / F)), (unsigned)nsrc, (unsigned)njobs), 64 * kGfWaves, args,
-                     (size_t)P * (5 * Q / 3) * F * 4, s, e0, e1);
+    if (c.form != kGfSplit || ja.seg) return hipErrorInvalidConfiguration;
+    int n = 0;
+    const GfFwdFn *t = gf_fwd_table(&n), *best = nullptr;
+    for (int i = 0; i < n; ++i)
+        if (t[i].T == c.T && t[i].g == c.g && (!best || t[i].many == (njobs > 4))) best = &t[i];
+    if (!best) return hipErrorInvalidConfiguration;
+    void *args[] = {(void *)&ja};
+    return gf_launch(best->fn, dim3(best->wgs, (unsigned)nsrc, (unsigned)njobs), 64 * kGfWaves, args, best->lds, s, e0,
+                     e1);
 }
 
 // The product kernels that exist: (a, M2) and their LDS.
@@ -655,8 +684,9 @@ static hipError_t gf_set_lds_limits(int maxb) {
     hipError_t e = hipSuccess;
     for (int i = 0; i < n && e == hipSuccess; ++i)
         e = hipFuncSetAttribute(t[i].fn, hipFuncAttributeMaxDynamicSharedMemorySize, maxb);
-    for (const void *f : {(const void *)k_gf_fwd<9, 9>, (const void *)k_gf_fwd<27, 9>, (const void *)k_gf_fwd<27, 27>})
-        if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, maxb);
+    const GfFwdFn *f = gf_fwd_table(&n);
+    for (int i = 0; i < n && e == hipSuccess; ++i)
+        e = hipFuncSetAttribute(f[i].fn, hipFuncAttributeMaxDynamicSharedMemorySize, maxb);
     return e;
 }
 
@@ -681,7 +711,7 @@ hipError_t launch_gf_inv(const GfChoice &c, const JobArgs &ja, int njobs, hipStr
     int g = c.g;
     void *args[] = {(void *)&ja, (void *)&g};
     const uint32_t words = (c.max_m + 63) / 64 * 2;
-    return gf_launch(fn, dim3((words + 63) / 64, (unsigned)njobs), 64 * kGfWaves, args, 0, s, e0, e1);
+    return gf_launch(fn, dim3((words + 62) / 63, (unsigned)njobs), 64 * kGfWaves, args, 0, s, e0, e1);
 }
 
 }  // namespace pa

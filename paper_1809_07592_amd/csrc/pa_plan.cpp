@@ -341,18 +341,17 @@ void plan_geometry(uint64_t L, const Geometry &g, LenPlan &lp, XTables *ct, XTab
 // ------------------------------------------------------- carry-less forms
 
 GfChoice gf_split_for(uint64_t bits, uint64_t words) {
-    // ascending capacity 32 T M: T, g, a, M2 = M / 3^a, F (divides g P)
+    // ascending capacity 32 T M: T, g, a, with M2 = M / 3^a
     static const struct {
-        int T, g, a, F;
-    } sizes[] = {{81, 1, 1, 9},   {81, 2, 1, 18},  {81, 3, 1, 27},  {243, 1, 2, 9},  {243, 2, 2, 18}, {243, 3, 2, 27},
-                 {243, 4, 2, 18}, {243, 5, 2, 15}, {729, 1, 2, 27}, {729, 3, 3, 27}};
+        int T, g, a;
+    } sizes[] = {{81, 1, 1},  {81, 2, 1},  {81, 3, 1},  {243, 1, 2}, {243, 2, 2},
+                 {243, 3, 2}, {243, 4, 2}, {243, 5, 2}, {729, 1, 2}, {729, 3, 3}};
     for (const auto &z : sizes) {
         GfChoice c;
         c.form = kGfSplit;
         c.T = z.T;
         c.g = z.g;
         c.a = z.a;
-        c.F = z.F;
         c.M2 = c.chunk_words() / (z.a == 1 ? 3 : z.a == 2 ? 9 : 27);
         if (c.cyclic_bits() >= bits && c.work_words() <= words) return c;
     }
