@@ -25,45 +25,74 @@ __device__ __forceinline__ uint32_t ld32_any(rsrc_t r, int o) {
     return (uint32_t)ld32(r, o);
 }
 
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 // One 16 x 16 x 128 binary product on the matrix cores: the operands hold
-// one bit per fp4 element, A's ones as 1.0 and B's as 0.5, so an
-// accumulator is half the count of common ones (exact in fp32 below 2^23)
-// and its fraction the parity.  Lane l holds 32 consecutive k of row
-// (column) l & 15 from k = 32 (l >> 4), as one 32-bit window; bit 4 p + j
-// goes to nibble p of register j, in both operands alike.
-__device__ __forceinline__ gf_v4i expand_a(uint32_t w) {
-    gf_v4i r = {(int)((w << 1) & 0x22222222u), (int)(w & 0x22222222u), (int)((w >> 1) & 0x22222222u),
-                (int)((w >> 2) & 0x22222222u)};
-    return r;
-}
-__device__ __forceinline__ gf_v4i expand_b(uint32_t w) {
-    gf_v4i r = {(int)(w & 0x11111111u), (int)((w >> 1) & 0x11111111u), (int)((w >> 2) & 0x11111111u),
-                (int)((w >> 3) & 0x11111111u)};
-    return r;
-}
+// one bit per fp4 element, ones as 0.5 in one operand where they are 1.0 in
+// the other, so a common one adds 0.5.  Accumulators start at 2^22, whose
+// last place is 0.5: sums stay exact up to 2^23 common ones, and the lowest
+// mantissa bit is the parity.  Lane l holds 32 consecutive k of row (column)
+// l & 15 from k = 32 (l >> 4), as one 32-bit window; the order of k inside
+// the four registers is free as long as both operands share it.
+constexpr float kGfBias = 4194304.0f;  // 2^22
 __device__ __forceinline__ gf_v4f bit_mfma(gf_v4i a, gf_v4i b, gf_v4f c) {
     const gf_v8i A = {a[0], a[1], a[2], a[3], 0, 0, 0, 0}, B = {b[0], b[1], b[2], b[3], 0, 0, 0, 0};
     return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A, B, c, 4, 4, 0, 0, 0, 0);
 }
+// Both operands from windows: bit 4 p + j in nibble p of register j.
+__device__ __forceinline__ gf_v4i expand_one(uint32_t w) {
+    gf_v4i r = {(int)((w << 1) & 0x22222222u), (int)(w & 0x22222222u), (int)((w >> 1) & 0x22222222u),
+                (int)((w >> 2) & 0x22222222u)};
+    return r;
+}
+__device__ __forceinline__ gf_v4i expand_half(uint32_t w) {
+    gf_v4i r = {(int)(w & 0x11111111u), (int)((w >> 1) & 0x11111111u), (int)((w >> 2) & 0x11111111u),
+                (int)((w >> 3) & 0x11111111u)};
+    return r;
+}
+// One operand expanded in LDS in units of 16 bits (8 bytes each, so that a
+// window at any multiple of 16 bits is 16 consecutive bytes): a unit holds
+// its bits 0, 4, 8, 12 and 1, 5, 9, 13 in the nibbles of the low and high
+// half of its first word, 2, 6, .. and 3, 7, .. in its second.  The even
+// bits are 1.0 and the odd ones 0.5 here, and the reverse in the window.
+__device__ __forceinline__ gf_v4i expand_units(uint32_t w) {
+    const uint32_t l = ((w << 1) & 0xFFFFu) | ((w << 15) & 0xFFFF0000u);
+    const uint32_t h = ((w >> 15) & 0xFFFEu) | ((w >> 1) & 0xFFFF0000u);
+    gf_v4i r = {(int)(l & 0x11112222u), (int)((l >> 2) & 0x11112222u), (int)(h & 0x11112222u),
+                (int)((h >> 2) & 0x11112222u)};
+    return r;
+}
+__device__ __forceinline__ gf_v4i expand_window(uint32_t w) {
+    const uint32_t l = __builtin_amdgcn_perm(w, w, 0x01000100u), h = __builtin_amdgcn_perm(w, w, 0x03020302u);
+    gf_v4i r = {(int)(l & 0x22221111u), (int)((l >> 2) & 0x22221111u), (int)(h & 0x22221111u),
+                (int)((h >> 2) & 0x22221111u)};
+    return r;
+}
 
-// The parities of one 16 x 16 tile as its 8 words: output bit 16 r + q of
-// row r, column q.  Accumulator v of lane l is row 4 (l >> 4) + v, column
-// l & 15, so ballot v holds row 4 h + v in its 16-bit field h.  Word j goes
-// to lane BASE + j of `into`.
-template <int BASE>
-__device__ __forceinline__ uint32_t tile_words(gf_v4f acc, uint32_t into) {
-    uint64_t b[4];
+// The parities of NT <= 8 tiles whose accumulator v in lane l is output bit
+// 16 (l & 15) + 4 (l >> 4) + v: lane l < 32 gets tiles 4 (l >> 4) .. + 3 as
+// 16-bit fields of row l & 15 (tiles 0, 1 in a, 2, 3 in b of lanes 0 .. 15).
+template <int NT>
+__device__ __forceinline__ uint2 tile_halfwords(const gf_v4f (&acc)[NT]) {
+    static_assert(NT <= 8, "eight nibbles a lane");
+    uint32_t x = 0;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) b[v] = __ballot(__builtin_amdgcn_fractf(acc[v]) != 0.0f);
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-    for (int h = 0; h < 4; ++h)
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const uint32_t lo = (uint32_t)(b[2 * p] >> (16 * h)) & 0xFFFFu;
-            const uint32_t hi = (uint32_t)(b[2 * p + 1] >> (16 * h)) & 0xFFFFu;
-            asm("v_writelane_b32 %0, %1, %2" : "+v"(into) : "s"(lo | (hi << 16)), "i"(BASE + 2 * h + p));
-        }
-    return into;
+        for (int v = 0; v < 4; ++v) x = funnel(__float_as_uint(acc[t][v]), x, 1);
+    x >>= 32 - 4 * NT;  // nibble t: bits 4 (l >> 4) .. + 3 of row l & 15, tile t
+    const uint32_t s = (threadIdx.x & 16u);  // odd rows of 16 lanes take tiles 4 ..
+    const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    auto bytes = [&](uint32_t v) PA_INLINE {  // four nibbles to four bytes
+        v = (v >> s) & 0xFFFFu;
+        v = (v | (v << 8)) & 0x00FF00FFu;
+        return (v | (v << 4)) & 0x0F0F0F0Fu;
+    };
+    const uint32_t y = bytes(p[0]) | (bytes(p[1]) << 4);
+    const auto q = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+    return make_uint2(__builtin_amdgcn_perm(q[1], q[0], 0x05010400u), __builtin_amdgcn_perm(q[1], q[0], 0x07030602u));
 }
 
 // Word w of the job's output: bits past m cleared, the head of the key
@@ -141,11 +170,13 @@ __global__ void __launch_bounds__(512) k_gf_direct(JobArgs ja) {
     };
     auto is_edge = [&](int u) PA_INLINE { return u == 0 || (u + 1) * (U * 128) + 160 > n; };
 
-    gf_v4f acc[NT] = {};
+    gf_v4f acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = gf_v4f{kGfBias, kGfBias, kGfBias, kGfBias};
     if (u0 < u1) {
         gf_v4i af[U];
 #pragma unroll
-        for (int f = 0; f < U - 2; ++f) af[f] = expand_a(fetch_a(u0 * U + f));
+        for (int f = 0; f < U - 2; ++f) af[f] = expand_one(fetch_a(u0 * U + f));
         uint32_t aw[U], bwd[U];
 #pragma unroll
         for (int s = 0; s < U; ++s) {
@@ -163,10 +194,10 @@ __global__ void __launch_bounds__(512) k_gf_direct(JobArgs ja) {
             }
 #pragma unroll
             for (int s = 0; s < U; ++s) {
-                af[(s + U - 2) % U] = expand_a(aw[s]);
-                const gf_v4i b = expand_b(bwd[s]);
+                af[(s + U - 2) % U] = expand_one(aw[s]);
+                const gf_v4i b = expand_half(bwd[s]);
 #pragma unroll
-                for (int t = 0; t < NT; ++t) acc[t] = bit_mfma(af[(s + 2 * t) % U], b, acc[t]);
+                for (int t = 0; t < NT; ++t) acc[t] = bit_mfma(b, af[(s + 2 * t) % U], acc[t]);
             }
 #pragma unroll
             for (int s = 0; s < U; ++s) {
@@ -177,9 +208,15 @@ __global__ void __launch_bounds__(512) k_gf_direct(JobArgs ja) {
     }
     // XOR of the waves' parities, 8 NT words per workgroup
     __shared__ uint32_t red[8][8 * NT];
-    uint32_t words = 0;
-    static_for_up<0, NT>([&](auto t) PA_INLINE { words = tile_words<8 * t>(acc[t], words); });
-    if (lane < 8 * NT) red[wave][lane] = words;
+    {
+        const uint2 hw = tile_halfwords<NT>(acc);
+        uint16_t *o = (uint16_t *)red[wave];
+        const int at = 64 * (lane >> 4) + q;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (lane < 32 && 4 * (lane >> 4) + i < NT)
+                o[at + 16 * i] = (uint16_t)((i & 2 ? hw.y : hw.x) >> (16 * (i & 1)));
+    }
     __syncthreads();
     if (threadIdx.x < 8 * NT) {
         uint32_t v = 0;
@@ -351,18 +388,18 @@ struct GfMul {
     static constexpr int tiles = (64 * M2 + 255) / 256, steps = (64 * M2 + 16 + 127) / 128;
     // tiles of one sweep over k (their row fragments stay in registers)
     static constexpr int sweeps = (tiles + 6) / 7, nt = (tiles + sweeps - 1) / sweeps;
-    static constexpr int waves = NP < kGfWaves ? NP : kGfWaves;
-    // LDS (words): five-third tables of X (then the products) and S (then
-    // the waves' expanded row operands), the reversed column operands, and
-    // the row operands
-    static constexpr int table = NP * 5 * M2;
-    static constexpr int units = 16 * nt * sweeps + 8 * steps;  // 16-bit steps of an expanded row operand
-    static constexpr int va = 4 * steps + 2, vb = 4 * M2 + 1;
-    static constexpr int region2 = table > waves * units * 4 ? table : waves * units * 4;
-    static constexpr int off_e = (table + 3) / 4 * 4, off_va = off_e + region2, off_vb = off_va + NP * va;
-    static constexpr int lds_words = off_vb + NP * vb;
-    static_assert(NP * va >= 4 * M, "the inverse transform's output reuses the column operands");
-    static_assert(NP * vb >= 3 * M, "the product reuses the row operands");
+    static constexpr int waves = NP < 8 ? 4 : 8;
+    // LDS (words): the five-third table of X (then the products), that of S
+    // (then the expanded row operands; two words per 16 bits of 128 M2), and
+    // the reversed column operands (then the inverse transform's output)
+    static constexpr int table = (NP * 5 * M2 + 3) / 4 * 4;
+    static constexpr int row = 16 * M2, over = 16 * (2 * nt * sweeps + steps);  // a fragment may end past its row
+    static constexpr int col = 4 * steps + 2, cols = NP * col > 4 * M ? NP * col : 4 * M;
+    // points whose row operands are in LDS together: all, or those of one r
+    static constexpr int passes = (2 * table + NP * row + over + cols) * 4 <= 80 * 1024 ? 1 : 2;
+    static constexpr int PP = NP / passes;
+    static constexpr int off_s = table, off_row = 2 * table, off_col = off_row + PP * row + over;
+    static constexpr int lds_words = off_col + cols;
 };
 
 template <int A, int M2>
@@ -373,7 +410,7 @@ __global__ void __launch_bounds__((64 * GfMul<A, M2>::waves)) k_gf_mul(JobArgs j
     const int tau = (int)blockIdx.x, tid = threadIdx.x;
     const int lane = tid & 63, wave = (int)uni((uint32_t)tid >> 6);
     uint32_t *lds = (uint32_t *)pa_lds;
-    uint32_t *tx = lds, *ts = lds + G::off_e, *va = lds + G::off_va, *vb = lds + G::off_vb;
+    uint32_t *tx = lds, *ts = lds + G::off_s, *rw = lds + G::off_row, *va = lds + G::off_col;
     const int32_t *S = resident ? job.Shat : job.S;
     const rsrc_t xr = make_rsrc(job.A + (size_t)tau * 2 * M, 2 * M * 4);
     const rsrc_t sr = make_rsrc(S + (size_t)tau * 2 * M, 2 * M * 4);
@@ -397,108 +434,104 @@ __global__ void __launch_bounds__((64 * GfMul<A, M2>::waves)) k_gf_mul(JobArgs j
         t[3 * M2] = lo ^ hi;
         t[4 * M2] = lo;
     }
-    for (int i = tid; i < NP * G::va; i += NTH) va[i] = 0;
+    for (int i = tid; i < NP * G::col; i += NTH) va[i] = 0;
     __syncthreads();
+#pragma unroll 1
+    for (int pass = 0; pass < G::passes; ++pass) {
+    const int first = pass * G::PP;  // the pass's points are first .. first + PP - 1
     // values at the points u^(3 i + r): sums of coefficients rotated by
     // (3 i + r) c U
-    for (int tk = tid; tk < 2 * NP * M2; tk += NTH) {
-        const bool second = tk >= NP * M2;
-        const int k = second ? tk - NP * M2 : tk;
-        const int pt = k / M2, p0 = k - pt * M2;
-        const int r = pt >= NA ? 2 : 1, step = U * (3 * (pt - (r - 1) * NA) + r);
+    for (int tk = tid; tk < 2 * G::PP * M2; tk += NTH) {
+        const bool second = tk >= G::PP * M2;
+        const int k = second ? tk - G::PP * M2 : tk;
+        const int at = k / M2, p0 = k - at * M2, pt = first + at;
+        const int r = pt >= NA ? 2 : 1;
+        const uint32_t step = (uint32_t)(U * (3 * (pt - (r - 1) * NA) + r));
         const uint32_t *t = (second ? ts : tx) + (r - 1) * NA * 5 * M2;
-        uint32_t b0 = 0, b1 = 0;
-        int qq = p0;
+        uint32_t b0 = 0, b1 = 0, qq = (uint32_t)p0;
 #pragma unroll
         for (int c = 0; c < NA; ++c) {
             b0 ^= t[c * 5 * M2 + qq];
             b1 ^= t[c * 5 * M2 + qq + 2 * M2];
-            qq -= step;
-            if (qq < 0) qq += 3 * M2;
+            qq = sub_mod(qq, step, 3 * M2);
         }
-        if (second) {
-            uint32_t *o = vb + pt * G::vb + p0;
-            o[0] = b0;
-            o[M2] = b0 ^ b1;
-            o[2 * M2] = b1;
-            o[3 * M2] = b0;
+        if (second) {  // the periodic sequence (b0, b0 + b1, b1, b0), expanded
+            gf_v4i *o = (gf_v4i *)(rw + at * G::row) + p0;
+            const gf_v4i e0 = expand_units(b0);
+            o[0] = e0;
+            o[M2] = expand_units(b0 ^ b1);
+            o[2 * M2] = expand_units(b1);
+            o[3 * M2] = e0;
         } else {  // bit-reversed as a whole, after one word of zeros
-            uint32_t *o = va + pt * G::va;
+            uint32_t *o = va + pt * G::col;
             o[2 * M2 - p0] = __builtin_bitreverse32(b0);
             o[M2 - p0] = __builtin_bitreverse32(b1);
         }
     }
     __syncthreads();
     // leaf products.  out[x] = sum_k row[x + k] col[k - q - 1] over the row
-    // operand's bits and the reversed column operand: as in the direct form,
-    // with the row windows (multiples of 16 bits) expanded once into LDS.
+    // operand's bits and the reversed column operand, x = 256 t + 16 r + q,
+    // as in the direct form.  Fragment k + 2 t of the row operand serves
+    // step k of tile t and later ones.
     {
-        uint32_t *ex = ts + wave * G::units * 4;
+        typedef gf_v4i __attribute__((aligned(8))) gf_v4i_a8;
         const int q = lane & 15, kb = lane >> 4;
-        for (int pt = wave; pt < NP; pt += G::waves) {
-            const uint32_t *row = vb + pt * G::vb;
-            for (int u = lane; u < 8 * M2; u += 64) {
-                const uint32_t w = funnel(row[(u >> 1) + 1], row[u >> 1], 16u * (uint32_t)(u & 1));
-                *(gf_v4i *)(ex + u * 4) = expand_a(w);
-            }
-            __builtin_amdgcn_wave_barrier();
-            const uint32_t *col = va + pt * G::va + kb;
-            const uint32_t *rowx = ex + (q + 2 * kb) * 4;
+        for (int at = wave; at < G::PP; at += G::waves) {
+            const int pt = first + at;
+            const uint32_t *cl = va + pt * G::col + kb;
+            const uint32_t *rx = rw + at * G::row + (q + 2 * kb) * 2;
 #pragma unroll 1
-            for (int sw = 0; sw < G::sweeps; ++sw) {
+            for (int sw = 0; sw < G::sweeps; ++sw, rx += G::nt * 32) {
                 constexpr int NT = G::nt, ST = G::steps;
-                const uint32_t *rx = rowx + sw * NT * 64;
-                gf_v4f acc[NT] = {};
+                gf_v4f acc[NT];
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[t] = gf_v4f{kGfBias, kGfBias, kGfBias, kGfBias};
                 gf_v4i af[ST + 2 * NT - 2];
 #pragma unroll
                 for (int k = 0; k < ST; ++k) {
-                    const gf_v4i b = expand_b(funnel(col[4 * k + 1], col[4 * k], (uint32_t)(31 - q)));
+                    const gf_v4i b = expand_window(funnel(cl[4 * k + 1], cl[4 * k], (uint32_t)(31 - q)));
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
-                        // fragment k + 2 t, read at its first use
-                        if (k < 2 || t == NT - 1) af[k + 2 * t] = *(const gf_v4i *)(rx + (k + 2 * t) * 32);
-                        acc[t] = bit_mfma(af[k + 2 * t], b, acc[t]);
+                        if (k < 2 || t == NT - 1) af[k + 2 * t] = *(const gf_v4i_a8 *)(rx + (k + 2 * t) * 16);
+                        acc[t] = bit_mfma(b, af[k + 2 * t], acc[t]);
                     }
                 }
-                // out words 0 .. M2 - 1 are the high half, then the low half
-                uint32_t w0 = 0;
-                static_for_up<0, NT>([&](auto t) PA_INLINE { w0 = tile_words<8 * t>(acc[t], w0); });
-                uint32_t *o = tx + pt * 5 * M2;
-                auto put = [&](int x, uint32_t v) PA_INLINE {
-                    if (x < M2) {
-                        o[2 * M2 + x] = v;
-                    } else if (x < 2 * M2) {
-                        o[x - M2] = v;
-                        o[x + 2 * M2] = v;
-                    }
-                };
-                if (lane < 8 * NT) put(sw * NT * 8 + lane, w0);
+                // out halves 0 .. 2 M2 - 1 are the element's high part, then
+                // its low part
+                const uint2 hw = tile_halfwords<NT>(acc);
+                uint16_t *o = (uint16_t *)(tx + pt * 5 * M2);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int t = 4 * kb + i, x = 16 * (sw * NT + t) + q;
+                    if (kb < 2 && t < NT && x < 4 * M2)
+                        o[x < 2 * M2 ? x + 4 * M2 : x - 2 * M2] = (uint16_t)((i & 2 ? hw.y : hw.x) >> (16 * (i & 1)));
+                }
             }
             __builtin_amdgcn_wave_barrier();
             for (int x = lane; x < M2; x += 64) {
                 uint32_t *o = tx + pt * 5 * M2 + x;
-                const uint32_t v = o[0] ^ o[2 * M2];
+                const uint32_t lo = o[0], v = lo ^ o[2 * M2];
                 o[M2] = v;
+                o[3 * M2] = lo;
                 o[4 * M2] = v;
             }
         }
     }
     __syncthreads();
+    }
     // inverse: coefficient c modulo z^NA - v^(r M2)
     for (int tk = tid; tk < 2 * M; tk += NTH) {
         const int r = tk >= M ? 2 : 1, k = tk - (r - 1) * M;
         const int c = k / M2, p0 = k - c * M2;
         const uint32_t *t = tx + (r - 1) * NA * 5 * M2;
         uint32_t b0 = 0, b1 = 0;
-        const int step = (3 * U * c) % (3 * M2);
-        int qq = p0 + U * r * c;
-        if (qq >= 3 * M2) qq -= 3 * M2;
+        const uint32_t step = (uint32_t)(3 * U * c);  // < 3 M2, as is U r c
+        uint32_t qq = add_mod((uint32_t)p0, (uint32_t)(U * r * c), 3 * M2);
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
             b0 ^= t[i * 5 * M2 + qq];
             b1 ^= t[i * 5 * M2 + qq + 2 * M2];
-            qq += step;
-            if (qq >= 3 * M2) qq -= 3 * M2;
+            qq = add_mod(qq, step, 3 * M2);
         }
         va[tk] = b0;          // [r][c][p0], low halves, then high halves
         va[2 * M + tk] = b1;
@@ -523,9 +556,9 @@ __global__ void __launch_bounds__((64 * GfMul<A, M2>::waves)) k_gf_mul(JobArgs j
                 c0 ^= top;
                 c1 ^= hi_of(NA - 1, o) ^ top;
             }
-            vb[p] = c0;
-            vb[M + p] = c0 ^ c1;
-            vb[2 * M + p] = c1;
+            ts[p] = c0;
+            ts[M + p] = c0 ^ c1;
+            ts[2 * M + p] = c1;
         }
     }
     __syncthreads();
@@ -536,7 +569,7 @@ __global__ void __launch_bounds__((64 * GfMul<A, M2>::waves)) k_gf_mul(JobArgs j
         for (int p = tid; p < 3 * M; p += NTH) {
             int k = p + d;
             if (k >= 3 * M) k -= 3 * M;
-            st32(ho, p * 4, (int)(vb[p] ^ vb[k]));
+            st32(ho, p * 4, (int)(ts[p] ^ ts[k]));
         }
     }
 }
