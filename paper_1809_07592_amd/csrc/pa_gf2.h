@@ -38,7 +38,7 @@ struct GfChoice {
     int chunk_words() const { return T / 3 * g; }                             // M
     uint64_t cyclic_bits() const { return 32ull * T * (uint64_t)chunk_words(); }
     uint64_t spectrum_words() const { return 2ull * T * chunk_words(); }      // X and the seed's spectrum
-    uint64_t work_words() const { return 5ull * T * chunk_words(); }          // X, then the products (3 T M)
+    uint64_t work_words() const { return 6ull * T * chunk_words(); }          // X, then the products (4 T M)
 };
 
 // Split of a cyclic product of at least `bits` bits whose work area fits in

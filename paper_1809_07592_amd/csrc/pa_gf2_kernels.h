@@ -267,11 +267,16 @@ __device__ __forceinline__ uint32_t add_mod(uint32_t a, uint32_t b, uint32_t n) 
 // every chunk, rotated, into tile t0, and a length-P transform over t0
 // follows.  Word positions split into classes modulo Cm = G P that no
 // rotation of the second step leaves; a workgroup takes one rho and F
-// classes (F divides Cm), so its tile is P x Q x F words.  What bounds it
-// is vector issue: a chunk word costs its load, three operations for its
-// target's address and an LDS exclusive or, and every word is read by Q
-// workgroups (from the caches).  Everything but rho is a constant, since
-// run-time divisions by the unit cost four times the rest.
+// classes (F divides Cm), so its tile is P x Q x F words.
+//
+// What bounds it is vector issue and the LDS.  So the rotations cost no
+// vector operation: a chunk's target row is its first row plus rho t1 (mod
+// Q), the chunks are taken in the order that makes rho t1 = D k for k = 0,
+// 1, .. (D = gcd(rho, Q); D chunks share each target and are added first),
+// a scalar row offset, and tiles have 2 Q rows, so that rows never wrap and
+// D k is an immediate offset.  The same in the second step: every wave has
+// one sigma, so a tile's rotation is a scalar.  Everything but rho is a
+// constant.  256 blocks of 10^6 bits: 341 us with per-word rotations.
 // Grid: (Q Cm / F, sources, jobs), 9 waves.  Wave w owns tiles t0 = w,
 // w + 9, ...: nothing else writes them before the barrier.
 constexpr int kGfWaves = 9;
@@ -279,12 +284,12 @@ constexpr int kGfWaves = 9;
 template <int Q, int P, int G, int F>
 __global__ void __launch_bounds__(64 * kGfWaves) k_gf_fwd(JobArgs ja) {
     constexpr int T = P * Q, Q3 = Q / 3, M = T / 3 * G, Cm = G * P, NF = Cm / F;
-    static_assert(P % kGfWaves == 0 && Q % 9 == 0 && Cm % F == 0, "tiles are dealt to 9 waves, rows unrolled by 9");
-    constexpr int third = Q3 * F, period = Q * F, trow = 5 * third;  // words of a tile: five thirds
+    static_assert(P % kGfWaves == 0 && (Q == 9 || Q == 27) && Cm % F == 0, "tiles are dealt to 9 waves");
+    constexpr int third = Q3 * F, period = Q * F, trow = 2 * period;  // words of a tile: two periods
     const bool src = blockIdx.y != 0;
     const JobDesc job = job_of(ja, uni(blockIdx.z));
     const int rho = (int)blockIdx.x / NF, f0 = ((int)blockIdx.x - rho * NF) * F;
-    uint32_t *tile = (uint32_t *)pa_lds;  // [P][5 Q / 3][F]
+    uint32_t *tile = (uint32_t *)pa_lds;  // [P][2 Q][F]
     const int lane = threadIdx.x & 63, wave = (int)uni(threadIdx.x >> 6);
 
     // word W of the source is bits [32 W, 32 W + 32) from bit `off` of the
@@ -293,82 +298,105 @@ __global__ void __launch_bounds__(64 * kGfWaves) k_gf_fwd(JobArgs ja) {
     const uint32_t off = src ? 0u : job.key_off, rem = off & 31u;
     const rsrc_t in = make_rsrc((const uint32_t *)(src ? job.seed : job.key) + (off >> 5),
                                 ((rem + (uint32_t)nbits + 31) / 32 * 4));
-    const int last = (nbits - 1) >> 5;  // the last word, cut to its valid bits
-    const uint32_t last_mask = ~0u >> (31 - ((nbits - 1) & 31));
-    const int rows = last / M + 1;      // chunks that hold bits
+    const int last = (nbits - 1) >> 5;
+
+    // the Q chunks of a tile in the order of their targets: slot k D + b is
+    // chunk t1 = (k inv mod K) + K b, K = Q / D, inv = (rho / D)^-1 mod K (the
+    // 17th power: the orders of the units mod 27, 9 and 3 divide 18).  Each
+    // lane finds one slot's offset; loads take them as scalars.
+    const int D = rho % 3 ? 1 : rho % 9 ? 3 : Q == 9 || rho % 27 ? 9 : Q;
+    int slot;
+    {
+        const uint32_t K = (uint32_t)(Q / D), r = (uint32_t)(rho / D) % K, k = (uint32_t)(lane / D);
+        uint32_t inv = r * r % K;
+        inv = inv * inv % K;
+        inv = inv * inv % K;
+        inv = inv * inv % K * r % K;
+        slot = (int)(k * inv % K + K * (uint32_t)(lane - (int)k * D)) * (P * M * 4);
+    }
 
     for (int t0 = wave; t0 < P; t0 += kGfWaves) {
         uint32_t *tl = tile + t0 * trow;
-        for (int i = lane; i < period; i += 64) tl[i] = 0;
+        for (int i = lane; i < trow; i += 64) tl[i] = 0;
         const int s0 = G * ((rho * t0) % T), sc = s0 % Cm, si = s0 / Cm;
+        int off_k[Q];
+#pragma unroll
+        for (int k = 0; k < Q; ++k) off_k[k] = __builtin_amdgcn_readlane(slot, k);
         for (int l = lane; l < third; l += 64) {
             const int i1 = l / F, f = l - i1 * F;
             int c = f0 + f - sc;  // class of the source word
             const int wrap = c < 0 ? 1 : 0;
             c += wrap ? Cm : 0;
             const int e = c + Cm * i1;  // its word in the chunk
-            // target: row (i1 + wrap + si + rho t1) mod Q
-            uint32_t at = (uint32_t)((i1 + wrap + si) * F);
-            at = min(at, at - (uint32_t)period);
-            // t1 = 0 .. Q - 1: all loads in flight, then the exclusive ors
-            // (whole groups of nine past the source's end are skipped)
+            int row = i1 + wrap + si;   // target row for t1 = 0, of 2 Q
+            row -= row >= Q ? Q : 0;
+            uint32_t *dst = tl + row * F + f;
+            const int at = (t0 * M + e) * 4;
             uint32_t w[Q];
 #pragma unroll
-            for (int b = 0; b < Q; b += 9)
-                if (t0 + P * b < rows) {
+            for (int k = 0; k < Q; ++k) w[k] = __builtin_amdgcn_raw_buffer_load_b32(in, at, off_k[k], 0);
+            if (rem) {
+                uint32_t h[Q];
 #pragma unroll
-                    for (int k = b; k < b + 9; ++k)
-                        w[k] = __builtin_amdgcn_raw_buffer_load_b32(in, e * 4, (t0 + P * k) * (M * 4), 0);
-                    if (rem) {
+                for (int k = 0; k < Q; ++k) h[k] = __builtin_amdgcn_raw_buffer_load_b32(in, at + 4, off_k[k], 0);
 #pragma unroll
-                        for (int k = b; k < b + 9; ++k)
-                            w[k] = funnel(__builtin_amdgcn_raw_buffer_load_b32(in, e * 4 + 4, (t0 + P * k) * (M * 4), 0),
-                                          w[k], rem);
-                    }
+                for (int k = 0; k < Q; ++k) w[k] = funnel(h[k], w[k], rem);
+            }
+            auto scatter = [&](auto d) PA_INLINE {
+                constexpr int DD = decltype(d)::value;
+#pragma unroll
+                for (int k = 0; k < Q / DD; ++k) {
+                    uint32_t x = w[k * DD];
+#pragma unroll
+                    for (int b = 1; b < DD; ++b) x ^= w[k * DD + b];
+                    atomicXor(dst + k * (DD * F), x);
                 }
+            };
+            if (D == 1) scatter(std::integral_constant<int, 1>{});
+            else if (D == 3) scatter(std::integral_constant<int, 3>{});
+            else if (D == 9) scatter(std::integral_constant<int, 9>{});
+            else scatter(std::integral_constant<int, Q>{});
+            // take back what lies past the source's last bit: the rest of
+            // its last word and, if words are shifted, the word after
 #pragma unroll
-            for (int b = 0; b < Q; b += 9)
-                if (t0 + P * b < rows) {
-#pragma unroll
-                    for (int k = b; k < b + 9; ++k) {
-                        const int t = t0 + P * k;
-                        if (t >= rows - 1) {  // uniform
-                            const int W = t * M + e;
-                            w[k] = W > last ? 0u : W == last ? w[k] & last_mask : w[k];
-                        }
-                        atomicXor(tl + f + at, w[k]);
-                        at = add_mod(at, (uint32_t)(rho * F), (uint32_t)period);
-                    }
+            for (int d = 0; d < 2; ++d) {
+                const int W = last + d, t = W / M;
+                if (t % P == t0 && W - t * M == e && t < T) {
+                    const uint32_t lo = (uint32_t)ld32(in, W * 4), hi = rem ? (uint32_t)ld32(in, W * 4 + 4) : 0u;
+                    const uint32_t keep = d ? 0u : ~0u >> (31 - ((nbits - 1) & 31));
+                    atomicXor(dst + rho * (t / P) % Q * F, funnel(hi, lo, rem) & ~keep);
                 }
+            }
         }
-        // to periodic form, five thirds
+        // to periodic form, two periods
         for (int l = lane; l < third; l += 64) {
-            const uint32_t a = tl[l], b = tl[l + third], c = tl[l + 2 * third];
-            tl[l] = a ^ c;
-            tl[l + third] = a ^ b;
-            tl[l + 2 * third] = b ^ c;
-            tl[l + 3 * third] = a ^ c;
-            tl[l + 4 * third] = a ^ b;
+            const uint32_t a = tl[l] ^ tl[l + period], b = tl[l + third] ^ tl[l + third + period],
+                           c = tl[l + 2 * third] ^ tl[l + 2 * third + period];
+            tl[l] = tl[l + period] = a ^ c;
+            tl[l + third] = tl[l + third + period] = a ^ b;
+            tl[l + 2 * third] = tl[l + 2 * third + period] = b ^ c;
         }
     }
     __syncthreads();
     const rsrc_t xo = make_rsrc(src ? job.S : job.A, (uint32_t)(2 * T * M * 4));
-    for (int tk = threadIdx.x; tk < P * third; tk += 64 * kGfWaves) {
-        const int sg = tk / third, l = tk - sg * third;
-        const int i = l / F, f = l - i * F;
-        const uint32_t step = (uint32_t)(Q / P * sg * F);
-        uint32_t j = (uint32_t)(i * F);
-        uint32_t lo = 0, hi = 0;
+    for (int sg = wave; sg < P; sg += kGfWaves) {
+        // tile t0 rotated by (Q / P) sigma t0 rows, as a word offset
+        const int turn = lane * trow + (Q - Q / P * sg * lane % Q) * F;
+        int off_t[P];
 #pragma unroll
-        for (int t0 = 0; t0 < P; ++t0) {
-            const uint32_t *tl = tile + t0 * trow + f + j;
-            lo ^= tl[0];
-            hi ^= tl[2 * third];
-            j = sub_mod(j, step, (uint32_t)period);
+        for (int t0 = 0; t0 < P; ++t0) off_t[t0] = __builtin_amdgcn_readlane(turn, t0);
+        for (int l = lane; l < third; l += 64) {
+            const int i = l / F, f = l - i * F;
+            uint32_t lo = 0, hi = 0;
+#pragma unroll
+            for (int t0 = 0; t0 < P; ++t0) {
+                lo ^= tile[off_t[t0] + l];
+                hi ^= tile[off_t[t0] + l + 2 * third];
+            }
+            const int at = ((rho + Q * sg) * (2 * M) + i * Cm + f0 + f) * 4;
+            st32(xo, at, (int)lo);
+            st32(xo, at + M * 4, (int)hi);
         }
-        const int at = ((rho + Q * sg) * (2 * M) + i * Cm + f0 + f) * 4;
-        st32(xo, at, (int)lo);
-        st32(xo, at + M * 4, (int)hi);
     }
 }
 
@@ -380,7 +408,7 @@ __global__ void __launch_bounds__(64 * kGfWaves) k_gf_fwd(JobArgs ja) {
 // 2 * 3^a products there are binary Toeplitz products on the matrix cores:
 // with the periodic sequence of one factor, output x is the plain
 // correlation at x for 0 <= x < 64 M2, so no reduction follows.
-template <int A, int M2>
+template <int A, int M2, int W>
 struct GfMul {
     static constexpr int NA = A == 1 ? 3 : A == 2 ? 9 : 27;
     static constexpr int NP = 2 * NA, M = NA * M2, U = M2 / NA;
@@ -388,7 +416,7 @@ struct GfMul {
     static constexpr int tiles = (64 * M2 + 255) / 256, steps = (64 * M2 + 16 + 127) / 128;
     // tiles of one sweep over k (their row fragments stay in registers)
     static constexpr int sweeps = (tiles + 6) / 7, nt = (tiles + sweeps - 1) / sweeps;
-    static constexpr int waves = NP < 8 ? 4 : 8;
+    static constexpr int waves = W;
     // LDS (words): the five-third table of X (then the products), that of S
     // (then the expanded row operands; two words per 16 bits of 128 M2), and
     // the reversed column operands (then the inverse transform's output)
@@ -402,9 +430,9 @@ struct GfMul {
     static constexpr int lds_words = off_col + cols;
 };
 
-template <int A, int M2>
-__global__ void __launch_bounds__((64 * GfMul<A, M2>::waves)) k_gf_mul(JobArgs ja, int T, int g, int resident) {
-    using G = GfMul<A, M2>;
+template <int A, int M2, int W>
+__global__ void __launch_bounds__(64 * W) k_gf_mul(JobArgs ja, int T, int g, int resident) {
+    using G = GfMul<A, M2, W>;
     constexpr int NA = G::NA, NP = G::NP, M = G::M, U = G::U, NTH = 64 * G::waves;
     const JobDesc job = job_of(ja, uni(blockIdx.y));
     const int tau = (int)blockIdx.x, tid = threadIdx.x;
@@ -562,55 +590,75 @@ __global__ void __launch_bounds__((64 * GfMul<A, M2>::waves)) k_gf_mul(JobArgs j
         }
     }
     __syncthreads();
-    // with the overlap of the chunk before: beta[p] + beta[p + 2M - g tau]
+    // with the overlap of the chunk before: beta[p] + beta[p + 2M - g tau],
+    // one period and its first third again
     {
-        const rsrc_t ho = make_rsrc(job.A + (size_t)T * 2 * M + (size_t)tau * 3 * M, 3 * M * 4);
+        const rsrc_t ho = make_rsrc(job.A + (size_t)T * 2 * M + (size_t)tau * 4 * M, 4 * M * 4);
         const int d = (2 * M + 3 * M - (g * tau) % (3 * M)) % (3 * M);
         for (int p = tid; p < 3 * M; p += NTH) {
             int k = p + d;
             if (k >= 3 * M) k -= 3 * M;
-            st32(ho, p * 4, (int)(ts[p] ^ ts[k]));
+            const int v = (int)(ts[p] ^ ts[k]);
+            st32(ho, p * 4, v);
+            if (p < M) st32(ho, (p + 3 * M) * 4, v);
         }
     }
 }
 
 // P3: word W = t M + e of the cyclic product is the sum over tau of word
-// e + g t tau (modulo 3 M) of product tau.  A workgroup forms 64 words, its
-// waves share tau; output words start at bit n - 1, so 64 words give 63
-// shifted ones.  Grid: (ceil(output words / 63), jobs).
+// e + g t tau (modulo 3 M) of product tau (whose rows hold 4 M words, so
+// that e needs no wrap).  A workgroup takes 64 consecutive words of one t
+// from word 63 s; its waves share tau, and each lane finds one product's
+// offset, which the loads take as a scalar.  The output starts at bit
+// n - 1, so each word also takes bits of the next one and 64 words give 63;
+// in a row's last segment the word after the row belongs to t + 1, and the
+// offsets are formed by lane.  The reads (L2) bound it.
+// Grid: (segments of 63 words of each t that the output can meet, jobs).
 template <int T>
 __global__ void __launch_bounds__(64 * kGfWaves) k_gf_inv(JobArgs ja, int g) {
     static_assert(T % kGfWaves == 0, "waves share tau evenly");
     constexpr int K = T / kGfWaves;
     const JobDesc job = job_of(ja, uni(blockIdx.y));
-    const int M = T / 3 * g, M3 = 3 * M;
-    const uint32_t words = (job.m + 63u) / 64u * 2u;
-    if (blockIdx.x * 63u >= words) return;
+    const int M = T / 3 * g, segs = (M + 62) / 63;
+    const int words = (int)((job.m + 63u) / 64u * 2u), W0 = (int)((job.n - 1u) / 32u);
+    const int row = (int)blockIdx.x / segs, t = W0 / M + row, e0 = ((int)blockIdx.x - row * segs) * 63;
+    const int w0 = t * M + e0 - W0;  // output word of lane 0
+    if (w0 >= words || w0 + 63 <= 0 || t >= T) return;
     const int lane = threadIdx.x & 63, wave = (int)uni(threadIdx.x >> 6);
-    const uint32_t w = blockIdx.x * 63u + (uint32_t)lane, W = (job.n - 1u) / 32u + w;
-    const int t = (int)(W / (uint32_t)M), e = (int)(W - (uint32_t)t * (uint32_t)M);
-    const rsrc_t h = make_rsrc(job.A + (size_t)T * 2 * M, (uint32_t)(T * M3 * 4));
-    const int tm = t % T;  // (past the last chunk: only for words past the output)
-    uint32_t p = add_mod((uint32_t)e, (uint32_t)(g * ((tm * (wave * K)) % T)), (uint32_t)M3) * 4u;
-    const uint32_t step = (uint32_t)(g * tm) * 4u, period = (uint32_t)M3 * 4u;
+    const rsrc_t h = make_rsrc(job.A + (size_t)T * 2 * M, (uint32_t)(T * 4 * M * 4));
+    const int first = wave * K;  // the wave's products
     uint32_t acc = 0;
-    const int base = wave * K * M3 * 4;
+    if (e0 + 63 < M) {
+#pragma unroll
+        for (int b = 0; b < K; b += 27) {
+            constexpr int N = K < 27 ? K : 27;
+            const int tau = first + b + lane;
+            const int at = (tau * 4 * M + g * ((t * tau) % T) + e0) * 4;
+#pragma unroll
+            for (int k = 0; k < N; ++k)
+                acc ^= (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(h, lane * 4, __builtin_amdgcn_readlane(at, k), 0);
+        }
+    } else {
+        const int e = e0 + lane, tl = e < M ? t : t + 1 < T ? t + 1 : 0, el = e < M ? e : 0;
+        const uint32_t step = (uint32_t)(4 * g * tl), period = (uint32_t)(12 * M);
+        uint32_t p = (uint32_t)(4 * g * ((tl * first) % T));
 #pragma unroll 27
-    for (int k = 0; k < K; ++k) {
-        acc ^= (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(h, (int)p, base + k * M3 * 4, 0);
-        p = add_mod(p, step, period);
+        for (int k = 0; k < K; ++k) {
+            acc ^= (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(h, (int)p + el * 4, (first + k) * (16 * M), 0);
+            p = add_mod(p, step, period);
+        }
     }
     __shared__ uint32_t red[kGfWaves][64];
-    __shared__ uint32_t sum[65];
     red[wave][lane] = acc;
     __syncthreads();
     if (wave == 0) {
 #pragma unroll
         for (int i = 1; i < kGfWaves; ++i) acc ^= red[i][lane];
-        sum[lane] = acc;
-        if (lane == 0) sum[64] = 0;
+        red[0][lane] = acc;
         __builtin_amdgcn_wave_barrier();
-        if (lane < 63 && w < words) OutWords(job).put(w, funnel(sum[lane + 1], acc, (job.n - 1u) & 31u));
+        const int w = w0 + lane;
+        if (lane < 63 && e0 + lane < M && w >= 0 && w < words)
+            OutWords(job).put((uint32_t)w, funnel(red[0][lane + 1], acc, (job.n - 1u) & 31u));
     }
 }
 
@@ -663,7 +711,7 @@ struct GfFwdFn {
 template <int Q, int P, int G, int F>
 static GfFwdFn gf_fwd_fn(bool many) {
     return {P * Q, G, F, many, (const void *)k_gf_fwd<Q, P, G, F>, (unsigned)(Q * (G * P / F)),
-            (size_t)P * (5 * Q / 3) * F * 4};
+            (size_t)P * 2 * Q * F * 4};
 }
 static const GfFwdFn *gf_fwd_table(int *count) {
     static const GfFwdFn table[] = {
@@ -689,23 +737,28 @@ hipError_t launch_gf_fwd(const GfChoice &c, int nsrc, const JobArgs &ja, int njo
                      e1);
 }
 
-// The product kernels that exist: (a, M2) and their LDS.
+// The product kernels that exist: (a, M2), waves, and their LDS.  Launches
+// of a few jobs have at most three workgroups a CU and take more waves each:
+// 12 for 18 points (two rounds of leaf products, even over the SIMDs).
 struct GfMulFn {
     int a, M2;
+    bool many;
     const void *fn;
     int threads;
     size_t lds;
 };
-template <int A, int M2>
-static GfMulFn gf_mul_fn() {
-    using G = GfMul<A, M2>;
+template <int A, int M2, int W>
+static GfMulFn gf_mul_fn(bool many) {
+    using G = GfMul<A, M2, W>;
     static_assert(G::lds_words * 4 <= 160 * 1024, "a workgroup's LDS");
-    return {A, M2, (const void *)k_gf_mul<A, M2>, 64 * G::waves, (size_t)G::lds_words * 4};
+    return {A, M2, many, (const void *)k_gf_mul<A, M2, W>, 64 * W, (size_t)G::lds_words * 4};
 }
 static const GfMulFn *gf_mul_table(int *count) {
-    static const GfMulFn table[] = {gf_mul_fn<1, 9>(),  gf_mul_fn<1, 18>(), gf_mul_fn<1, 27>(),
-                                    gf_mul_fn<2, 9>(),  gf_mul_fn<2, 18>(), gf_mul_fn<2, 27>(),
-                                    gf_mul_fn<2, 36>(), gf_mul_fn<2, 45>(), gf_mul_fn<3, 27>()};
+    static const GfMulFn table[] = {
+        gf_mul_fn<1, 9, 4>(true),   gf_mul_fn<1, 18, 4>(true),  gf_mul_fn<1, 27, 4>(true),  gf_mul_fn<2, 9, 8>(true),
+        gf_mul_fn<2, 18, 8>(true),  gf_mul_fn<2, 27, 8>(true),  gf_mul_fn<2, 36, 8>(true),  gf_mul_fn<2, 45, 8>(true),
+        gf_mul_fn<3, 27, 16>(true), gf_mul_fn<2, 9, 12>(false), gf_mul_fn<2, 18, 12>(false), gf_mul_fn<2, 27, 12>(false),
+        gf_mul_fn<2, 36, 12>(false), gf_mul_fn<2, 45, 12>(false)};
     *count = (int)(sizeof(table) / sizeof(table[0]));
     return table;
 }
@@ -729,10 +782,11 @@ hipError_t launch_gf_mul(const GfChoice &c, bool resident, const JobArgs &ja, in
     int n = 0, T = c.T, g = c.g, r = resident ? 1 : 0;
     const GfMulFn *t = gf_mul_table(&n);
     void *args[] = {(void *)&ja, (void *)&T, (void *)&g, (void *)&r};
+    const GfMulFn *best = nullptr;
     for (int i = 0; i < n; ++i)
-        if (t[i].a == c.a && t[i].M2 == c.M2)
-            return gf_launch(t[i].fn, dim3((unsigned)T, (unsigned)njobs), t[i].threads, args, t[i].lds, s, e0, e1);
-    return hipErrorInvalidConfiguration;
+        if (t[i].a == c.a && t[i].M2 == c.M2 && (!best || t[i].many == (T * njobs > 768))) best = &t[i];
+    if (!best) return hipErrorInvalidConfiguration;
+    return gf_launch(best->fn, dim3((unsigned)T, (unsigned)njobs), best->threads, args, best->lds, s, e0, e1);
 }
 
 hipError_t launch_gf_inv(const GfChoice &c, const JobArgs &ja, int njobs, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
@@ -743,8 +797,10 @@ hipError_t launch_gf_inv(const GfChoice &c, const JobArgs &ja, int njobs, hipStr
     if (c.form != kGfSplit || ja.seg) return hipErrorInvalidConfiguration;
     int g = c.g;
     void *args[] = {(void *)&ja, (void *)&g};
-    const uint32_t words = (c.max_m + 63) / 64 * 2;
-    return gf_launch(fn, dim3((words + 62) / 63, (unsigned)njobs), 64 * kGfWaves, args, 0, s, e0, e1);
+    // output words can begin anywhere in a row of M
+    const unsigned M = (unsigned)c.chunk_words(), words = (c.max_m + 63) / 64 * 2;
+    return gf_launch(fn, dim3(((words + M - 2) / M + 1) * ((M + 62) / 63), (unsigned)njobs), 64 * kGfWaves, args, 0, s,
+                     e0, e1);
 }
 
 }  // namespace pa
