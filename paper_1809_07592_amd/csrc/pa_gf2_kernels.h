@@ -41,17 +41,6 @@ __device__ __forceinline__ gf_v4f bit_mfma(gf_v4i a, gf_v4i b, gf_v4f c) {
     const gf_v8i A = {a[0], a[1], a[2], a[3], 0, 0, 0, 0}, B = {b[0], b[1], b[2], b[3], 0, 0, 0, 0};
     return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A, B, c, 4, 4, 0, 0, 0, 0);
 }
-// Both operands from windows: bit 4 p + j in nibble p of register j.
-__device__ __forceinline__ gf_v4i expand_one(uint32_t w) {
-    gf_v4i r = {(int)((w << 1) & 0x22222222u), (int)(w & 0x22222222u), (int)((w >> 1) & 0x22222222u),
-                (int)((w >> 2) & 0x22222222u)};
-    return r;
-}
-__device__ __forceinline__ gf_v4i expand_half(uint32_t w) {
-    gf_v4i r = {(int)(w & 0x11111111u), (int)((w >> 1) & 0x11111111u), (int)((w >> 2) & 0x11111111u),
-                (int)((w >> 3) & 0x11111111u)};
-    return r;
-}
 // One operand expanded in LDS in units of 16 bits (8 bytes each, so that a
 // window at any multiple of 16 bits is 16 consecutive bytes): a unit holds
 // its bits 0, 4, 8, 12 and 1, 5, 9, 13 in the nibbles of the low and high
@@ -69,6 +58,17 @@ __device__ __forceinline__ gf_v4i expand_window(uint32_t w) {
     gf_v4i r = {(int)(l & 0x22221111u), (int)((l >> 2) & 0x22221111u), (int)(h & 0x22221111u),
                 (int)((h >> 2) & 0x22221111u)};
     return r;
+}
+
+// The units of a word whose window is read in the other direction: each
+// 16-bit half bit-reversed, in place; the window's halves change places.
+__device__ __forceinline__ gf_v4i expand_units_reversed(uint32_t w) {
+    const gf_v4i r = expand_units(__builtin_bitreverse32(w));
+    return gf_v4i{r[2], r[3], r[0], r[1]};
+}
+__device__ __forceinline__ gf_v4i expand_window_swapped(uint32_t w) {
+    const gf_v4i r = expand_window(w);
+    return gf_v4i{r[2], r[3], r[0], r[1]};
 }
 
 // The parities of NT <= 8 tiles whose accumulator v in lane l is output bit
@@ -115,99 +115,94 @@ struct OutWords {
 // ------------------------------------------------------------------- direct
 //
 // y[i] = sum_j s[i - j + n - 1] x[j].  With xr the reversed key and
-// i = 256 R + 16 r + q this is sum_k s[256 R + 16 r + k] xr[k - q]: a matrix
+// i = 256 t + 16 r + q this is sum_k s[256 t + 16 r + k] xr[k - q]: a matrix
 // product whose row operand starts at a multiple of 16 bits of the seed and
-// whose column operand is the key shifted by its column, so both are 32-bit
-// windows of packed bits, expanded in registers.  A workgroup computes NT
-// tiles of 256 outputs; its waves (and the launch's slices) share k.  The
-// row operand depends on k + 256 R only: a step of k = 128 needs one new
-// row fragment for all NT tiles (the others are those of earlier steps, kept
-// in 2 NT rotating registers) and one column fragment.
-template <int NT, bool PARTS>
-__global__ void __launch_bounds__(512) k_gf_direct(JobArgs ja) {
-    constexpr int U = 2 * NT;  // steps per unrolled unit
+// whose column operand is the key shifted by its column.  A workgroup
+// computes NT tiles of 256 outputs; its waves (and the launch's slices)
+// share k.
+//
+// A wave goes through k in chunks of ST steps of 128: the chunk's seed words
+// are expanded once into LDS, so that a row fragment is 16 bytes read at
+// 8-byte alignment, and its key words are copied there; the next chunk's
+// words are loaded meanwhile.  The row operand depends on k + 256 t only:
+// a step needs one new row fragment for all NT tiles (the others are those
+// of earlier steps, kept in 2 NT rotating registers) and one column window,
+// expanded in nine operations.  So with NT = 4 the matrix cores (64 clocks a
+// step) bound it, with NT = 2 vector issue does.  The reversal is the
+// seed's: its words are expanded bit-reversed, and the two halves of a
+// window change places.  (Windows of both operands fetched from the caches
+// and expanded in registers, 27 vector operations a step: 32 blocks of 10^5
+// bits to 20,000 in 57 us.)
+template <int NT, int ST, int NW, bool PARTS>
+__global__ void __launch_bounds__(64 * NW) k_gf_direct(JobArgs ja) {
+    constexpr int U = 2 * NT, SW = 4 * ST + 8 * NT, KW = 4 * ST + 2;  // a chunk's seed and key words
     const JobDesc job = job_of(ja, uni(blockIdx.z));
     const int n = (int)job.n, R0 = (int)blockIdx.x * NT;
     if ((uint32_t)R0 * 256u >= job.m) return;
-    const int lane = threadIdx.x & 63, wave = (int)uni(threadIdx.x >> 6), nw = blockDim.x >> 6;
+    const int lane = threadIdx.x & 63, wave = (int)uni(threadIdx.x >> 6);
     const int q = lane & 15, kb = lane >> 4;
-    const int steps = (n + 15 + 127) / 128, units = (steps + U - 1) / U;
-    const int share = (int)gridDim.y * nw, per = (units + share - 1) / share;
-    const int u0 = min(units, ((int)blockIdx.y * nw + wave) * per), u1 = min(units, u0 + per);
+    constexpr int nw = NW;
+    const int chunks = (n + 15 + 128 * ST - 1) / (128 * ST);
+    const int share = (int)gridDim.y * nw, per = (chunks + share - 1) / share;
+    const int c0 = min(chunks, ((int)blockIdx.y * nw + wave) * per), c1 = min(chunks, c0 + per);
 
     const rsrc_t sb = make_rsrc(job.seed, (uint32_t)((job.seed_bits + 31) / 32 * 4));
     const int ko = (int)(job.key_off & 31u), last = (ko + n - 1) >> 5;
     const rsrc_t xb = make_rsrc((const uint32_t *)job.key + (job.key_off >> 5), (uint32_t)(last + 1) * 4);
-    // seed window of fragment f: word 8 R0 + 4 f + kb + (r >> 1), odd rows
-    // 16 bits on; key window of step k: bits from x0 - 128 k - 32 kb,
-    // reversed
-    const int aoff = (8 * R0 + kb + (q >> 1)) * 4;
-    const uint32_t ash = 16u * (uint32_t)(q & 1);
-    const int x0 = n + ko - 32 + q;
-    const int bw = (x0 >> 5) - kb;
-    const uint32_t bsh = (uint32_t)x0 & 31u;
     const uint32_t first_mask = ~0u << ko, last_mask = ~0u >> (31 - ((ko + n - 1) & 31));
 
-    auto fetch_a = [&](int f) PA_INLINE {
-        const uint32_t lo = (uint32_t)ld32(sb, aoff + f * 16), hi = (uint32_t)ld32(sb, aoff + f * 16 + 4);
-        return funnel(hi, lo, ash);
+    __shared__ __attribute__((aligned(16))) uint32_t rows_lds[nw][SW * 4];
+    __shared__ uint32_t keys_lds[nw][KW];
+    uint32_t *rows = rows_lds[wave], *keys = keys_lds[wave];
+    // the key window of step k starts at bit x0 + q - 128 k - 32 kb of the
+    // key's words; chunk c needs the words from top + 3 - 4 ST (c + 1)
+    const int x0 = n + ko - 32, top = x0 >> 5;
+    const uint32_t ksh = (uint32_t)(x0 + q) & 31u;
+    const uint32_t *kwin = keys + (3 - kb + (((x0 + q) >> 5) - top));
+    const uint32_t *rwin = rows + (q + 2 * kb) * 2;
+
+    auto key_word = [&](int w) PA_INLINE {
+        uint32_t v = ld32_any(xb, w * 4);
+        if (w == 0) v &= first_mask;
+        if (w == last) v &= last_mask;
+        return v;
     };
-    auto fetch_b = [&](int k, bool edge) PA_INLINE {
-        const int w = bw - 4 * k;
-        uint32_t lo, hi;
-        if (!edge) {  // (uniform)
-            lo = (uint32_t)ld32(xb, w * 4);
-            hi = (uint32_t)ld32(xb, w * 4 + 4);
-        } else {  // windows across the key's first or last word, or past them
-            lo = ld32_any(xb, w * 4);
-            hi = ld32_any(xb, w * 4 + 4);
-            if (w == 0) lo &= first_mask;
-            if (w == last) lo &= last_mask;
-            if (w + 1 == 0) hi &= first_mask;
-            if (w + 1 == last) hi &= last_mask;
-        }
-        return __builtin_bitreverse32(funnel(hi, lo, bsh));
+    uint32_t s0 = 0, s1 = 0, k0 = 0, k1 = 0;
+    auto fetch = [&](int c) PA_INLINE {
+        const int sw = R0 * 8 + c * (4 * ST), kw = top + 1 - 4 * ST * (c + 1);
+        if (lane < SW) s0 = (uint32_t)ld32(sb, (sw + lane) * 4);
+        if (lane < SW - 64) s1 = (uint32_t)ld32(sb, (sw + 64 + lane) * 4);
+        if (lane < KW) k0 = key_word(kw + lane);
+        if (lane < KW - 64) k1 = key_word(kw + 64 + lane);
     };
-    auto is_edge = [&](int u) PA_INLINE { return u == 0 || (u + 1) * (U * 128) + 160 > n; };
+    typedef gf_v4i __attribute__((aligned(8))) gf_v4i_a8;
+    auto fragment = [&](int f) PA_INLINE { return *(const gf_v4i_a8 *)(rwin + f * 16); };
 
     gf_v4f acc[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = gf_v4f{kGfBias, kGfBias, kGfBias, kGfBias};
-    if (u0 < u1) {
-        gf_v4i af[U];
+    if (c0 < c1) fetch(c0);
+    for (int c = c0; c < c1; ++c) {
+        if (lane < SW) ((gf_v4i *)rows)[lane] = expand_units_reversed(s0);
+        if (lane < SW - 64) ((gf_v4i *)rows)[64 + lane] = expand_units_reversed(s1);
+        if (lane < KW) keys[lane] = k0;
+        if (lane < KW - 64) keys[64 + lane] = k1;
+        __builtin_amdgcn_wave_barrier();
+        if (c + 1 < c1) fetch(c + 1);
+        gf_v4i row[ST + U - 2];
 #pragma unroll
-        for (int f = 0; f < U - 2; ++f) af[f] = expand_one(fetch_a(u0 * U + f));
-        uint32_t aw[U], bwd[U];
+        for (int f = 0; f < U - 2; ++f) row[f] = fragment(f);
 #pragma unroll
-        for (int s = 0; s < U; ++s) {
-            aw[s] = fetch_a(u0 * U + s + U - 2);
-            bwd[s] = fetch_b(u0 * U + s, is_edge(u0));
+        for (int k = 0; k < ST; ++k) {
+            row[k + U - 2] = fragment(k + U - 2);
+            const gf_v4i b = expand_window_swapped(funnel(kwin[4 * (ST - 1 - k) + 1], kwin[4 * (ST - 1 - k)], ksh));
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc[t] = bit_mfma(b, row[k + 2 * t], acc[t]);
         }
-        for (int u = u0; u < u1; ++u) {
-            uint32_t an[U], bn[U];
-            // the next unit's windows (past the end: the buffers' range
-            // check gives zeros, and nothing uses them)
-#pragma unroll
-            for (int s = 0; s < U; ++s) {
-                an[s] = fetch_a((u + 1) * U + s + U - 2);
-                bn[s] = fetch_b((u + 1) * U + s, is_edge(u + 1));
-            }
-#pragma unroll
-            for (int s = 0; s < U; ++s) {
-                af[(s + U - 2) % U] = expand_one(aw[s]);
-                const gf_v4i b = expand_half(bwd[s]);
-#pragma unroll
-                for (int t = 0; t < NT; ++t) acc[t] = bit_mfma(b, af[(s + 2 * t) % U], acc[t]);
-            }
-#pragma unroll
-            for (int s = 0; s < U; ++s) {
-                aw[s] = an[s];
-                bwd[s] = bn[s];
-            }
-        }
+        __builtin_amdgcn_wave_barrier();
     }
     // XOR of the waves' parities, 8 NT words per workgroup
-    __shared__ uint32_t red[8][8 * NT];
+    __shared__ uint32_t red[nw][8 * NT];
     {
         const uint2 hw = tile_halfwords<NT>(acc);
         uint16_t *o = (uint16_t *)red[wave];
@@ -220,6 +215,7 @@ __global__ void __launch_bounds__(512) k_gf_direct(JobArgs ja) {
     __syncthreads();
     if (threadIdx.x < 8 * NT) {
         uint32_t v = 0;
+#pragma unroll
         for (int w = 0; w < nw; ++w) v ^= red[w][threadIdx.x];
         const uint32_t wd = (uint32_t)R0 * 8u + threadIdx.x;
         if constexpr (PARTS) {
@@ -249,6 +245,12 @@ __global__ void __launch_bounds__(256) k_gf_parts(JobArgs ja, int slices) {
 // beta by s: sums of rotated elements need no reduction.  Two of the three
 // thirds determine the element; a table of five thirds (one period and two
 // more) gives lo and hi of a rotation at a linear index.
+
+__device__ __forceinline__ unsigned long long ld64(rsrc_t r, int voff, int soff) {
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
+    return (unsigned long long)v[1] << 32 | v[0];
+}
 
 // a - b (mod n) for 0 <= a, b < n as one subtraction, one addition and an
 // unsigned minimum.
@@ -681,12 +683,16 @@ hipError_t launch_gf_direct(const GfChoice &c, const JobArgs &ja, int njobs, hip
                             hipEvent_t e1) {
     const void *fn = nullptr;
     const bool parts = c.slices > 1;
-    if (c.nt == 4) fn = parts ? (const void *)k_gf_direct<4, true> : (const void *)k_gf_direct<4, false>;
-    if (c.nt == 8) fn = parts ? (const void *)k_gf_direct<8, true> : (const void *)k_gf_direct<8, false>;
+    int nw = 8;
+    // few workgroups: 16 waves that share the key in finer chunks
+    if (c.nt == 1) nw = 16, fn = parts ? (const void *)k_gf_direct<1, 8, 16, true> : (const void *)k_gf_direct<1, 8, 16, false>;
+    if (c.nt == 2) nw = 16, fn = parts ? (const void *)k_gf_direct<2, 8, 16, true> : (const void *)k_gf_direct<2, 8, 16, false>;
+    if (c.nt == 4) fn = parts ? (const void *)k_gf_direct<4, 16, 8, true> : (const void *)k_gf_direct<4, 16, 8, false>;
+    if (c.nt == 8) fn = parts ? (const void *)k_gf_direct<8, 16, 8, true> : (const void *)k_gf_direct<8, 16, 8, false>;
     if (c.form != kGfDirect || ja.seg || c.slices < 1) return hipErrorInvalidConfiguration;
     void *args[] = {(void *)&ja};
     const uint32_t per = 256u * (uint32_t)c.nt;
-    return gf_launch(fn, dim3((c.max_m + per - 1) / per, (unsigned)c.slices, (unsigned)njobs), 512, args, 0, s, e0, e1);
+    return gf_launch(fn, dim3((c.max_m + per - 1) / per, (unsigned)c.slices, (unsigned)njobs), 64 * nw, args, 0, s, e0, e1);
 }
 
 hipError_t launch_gf_parts(const GfChoice &c, const JobArgs &ja, int njobs, hipStream_t s, hipEvent_t e0,

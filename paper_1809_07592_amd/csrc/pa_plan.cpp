@@ -358,23 +358,40 @@ GfChoice gf_split_for(uint64_t bits, uint64_t words) {
     return GfChoice{};
 }
 
+// Direct up to where the split form is faster.  Measured (us, one block, back
+// to back): n = 200,000 to 50,000 direct 11.5, split 15; 262,144 to 65,536
+// 13.4 and 15; 300,000 to 60,000 15.0 and 15.  Many blocks: 32 of 100,000 to
+// 20,000 34.6 and 33.8, 32 of 200,000 to 40,000 83 and 94; from 10^6 bits the
+// split form takes 4 us a block, where the direct one takes 0.5 us for each
+// 10^9 products.
+//
+// Tiles a workgroup, and slices of the key: up to 2^17 key bits one launch
+// is faster than two (100,003 to 50,001: 9.1 against 9.7 with slices), with
+// few tiles a workgroup while that is what fills the chip (100,003 to
+// 25,001: 8.9 with one, 10.8 with four; 32 blocks of 100,000 to 20,000: 57
+// with two, 34.6 with four).  Longer keys leave too few workgroups, and a
+// serial chain in each, unless they are sliced (200,000 to 50,000: 14.6
+// unsliced, 11.7 with four tiles and eight slices).
 GfChoice gf_plain_for(uint64_t n, uint64_t m, uint64_t bits, uint64_t words, int njobs) {
+    GfChoice split = gf_split_for(bits, words);
+    split.max_m = (uint32_t)m;
     const double products = (double)n * (double)m;
+    double most = 1.75e10;
+    if (njobs > 1 && split.form == kGfSplit) most = std::min(8.0e9, 1.2e4 * (double)split.cyclic_bits());
+    if (products > most) return split;
     GfChoice c;
-    if (products <= (njobs == 1 ? 1.0e10 : 2.0e9)) {
-        c.form = kGfDirect;
-        c.nt = 4;
-        c.max_m = (uint32_t)m;
-        const uint64_t groups = (m + 1023) / 1024 * (uint64_t)njobs, units = (n + 15 + 1023) / 1024;
-        c.slices = 1;
-        if (units > 64) {
-            c.slices = (int)std::max<uint64_t>(1, std::min<uint64_t>(512 / std::max<uint64_t>(groups, 1), units / 16));
-            if (gf_direct_words(c) > words) c.slices = 1;
-        }
-        return c;
-    }
-    c = gf_split_for(bits, words);
+    c.form = kGfDirect;
     c.max_m = (uint32_t)m;
+    const uint64_t jobs = (uint64_t)njobs;
+    auto groups = [&](int nt) { return (m + 256 * nt - 1) / (256 * nt) * jobs; };
+    c.nt = groups(1) <= 256 ? 1 : njobs == 1 || groups(2) <= 384 ? 2 : 4;
+    c.slices = 1;
+    if (n > (1u << 17) && groups(4) < 160) {
+        const uint64_t chunks = (n + 15 + 2047) / 2048;  // of 16 steps
+        c.nt = 4;
+        c.slices = (int)std::min<uint64_t>(320 / groups(4), chunks / 8);
+        if (gf_direct_words(c) > words) c.slices = 1;
+    }
     return c;
 }
 
