@@ -271,45 +271,58 @@ __device__ __forceinline__ uint32_t add_mod(uint32_t a, uint32_t b, uint32_t n) 
 // rotation of the second step leaves; a workgroup takes one rho and F
 // classes (F divides Cm), so its tile is P x Q x F words.
 //
-// What bounds it is vector issue and the LDS.  So the rotations cost no
-// vector operation: a chunk's target row is its first row plus rho t1 (mod
+// The rotations cost no vector operation: a chunk's target row is its first row plus rho t1 (mod
 // Q), the chunks are taken in the order that makes rho t1 = D k for k = 0,
 // 1, .. (D = gcd(rho, Q); D chunks share each target and are added first),
 // a scalar row offset, and tiles have 2 Q rows, so that rows never wrap and
 // D k is an immediate offset.  The same in the second step: every wave has
 // one sigma, so a tile's rotation is a scalar.  Everything but rho is a
-// constant.  256 blocks of 10^6 bits: 341 us with per-word rotations.
-// Grid: (Q Cm / F, sources, jobs), 9 waves.  Wave w owns tiles t0 = w,
-// w + 9, ...: nothing else writes them before the barrier.
+// constant.  Then the loads bound it (address units busy 77% of the
+// time), so with whole classes (F = Cm, the words of a chunk in order) a
+// workgroup can take R = 2 values of rho that read the same words: rho and
+// Q - rho, whose targets are the same rows in the other direction.  With G
+// even, words go in pairs.  256 blocks of 10^6 bits: 341 us with per-word
+// rotations, 277 with scalar ones, 207 with two rho a workgroup.
+// Grid: (Q Cm / F, or (Q / 2 + 1) Cm / F with two rho, sources, jobs), 9
+// waves.  Wave w owns tiles t0 = w, w + 9, ...: nothing else writes them
+// before the barrier.
 constexpr int kGfWaves = 9;
 
-template <int Q, int P, int G, int F>
+template <int Q, int P, int G, int F, int R>
 __global__ void __launch_bounds__(64 * kGfWaves) k_gf_fwd(JobArgs ja) {
     constexpr int T = P * Q, Q3 = Q / 3, M = T / 3 * G, Cm = G * P, NF = Cm / F;
     static_assert(P % kGfWaves == 0 && (Q == 9 || Q == 27) && Cm % F == 0, "tiles are dealt to 9 waves");
+    static_assert(R == 1 || F == Cm, "a pair of rho reads the same words");
     constexpr int third = Q3 * F, period = Q * F, trow = 2 * period;  // words of a tile: two periods
+    // words a lane handles together: every rotation is a multiple of G, so
+    // with G even pairs stay pairs (half the loads, LDS operations and
+    // addresses)
+    constexpr int V = G % 2 == 0 && F % 2 == 0 ? 2 : 1;
+    typedef typename std::conditional<V == 2, unsigned long long, uint32_t>::type Wv;
     const bool src = blockIdx.y != 0;
     const JobDesc job = job_of(ja, uni(blockIdx.z));
-    const int rho = (int)blockIdx.x / NF, f0 = ((int)blockIdx.x - rho * NF) * F;
-    uint32_t *tile = (uint32_t *)pa_lds;  // [P][2 Q][F]
+    const int rho0 = (int)blockIdx.x / NF, f0 = ((int)blockIdx.x - rho0 * NF) * F;
+    const int nr = R == 2 && rho0 ? 2 : 1;  // values of rho: rho0 and Q - rho0
+    uint32_t *tile = (uint32_t *)pa_lds;    // [R][P][2 Q][F]
     const int lane = threadIdx.x & 63, wave = (int)uni(threadIdx.x >> 6);
 
     // word W of the source is bits [32 W, 32 W + 32) from bit `off` of the
-    // buffer, `rem` of its first word
+    // buffer, `rem` of its first word; a source that starts at bit 0 is
+    // whole 64-bit words
     const int nbits = (int)(src ? job.seed_bits : job.n);
     const uint32_t off = src ? 0u : job.key_off, rem = off & 31u;
     const rsrc_t in = make_rsrc((const uint32_t *)(src ? job.seed : job.key) + (off >> 5),
-                                ((rem + (uint32_t)nbits + 31) / 32 * 4));
+                                off ? (rem + (uint32_t)nbits + 31) / 32 * 4 : ((uint32_t)nbits + 63) / 64 * 8);
     const int last = (nbits - 1) >> 5;
 
     // the Q chunks of a tile in the order of their targets: slot k D + b is
     // chunk t1 = (k inv mod K) + K b, K = Q / D, inv = (rho / D)^-1 mod K (the
     // 17th power: the orders of the units mod 27, 9 and 3 divide 18).  Each
     // lane finds one slot's offset; loads take them as scalars.
-    const int D = rho % 3 ? 1 : rho % 9 ? 3 : Q == 9 || rho % 27 ? 9 : Q;
+    const int D = rho0 % 3 ? 1 : rho0 % 9 ? 3 : Q == 9 || rho0 % 27 ? 9 : Q;
     int slot;
     {
-        const uint32_t K = (uint32_t)(Q / D), r = (uint32_t)(rho / D) % K, k = (uint32_t)(lane / D);
+        const uint32_t K = (uint32_t)(Q / D), r = (uint32_t)(rho0 / D) % K, k = (uint32_t)(lane / D);
         uint32_t inv = r * r % K;
         inv = inv * inv % K;
         inv = inv * inv % K;
@@ -319,85 +332,135 @@ __global__ void __launch_bounds__(64 * kGfWaves) k_gf_fwd(JobArgs ja) {
 
     for (int t0 = wave; t0 < P; t0 += kGfWaves) {
         uint32_t *tl = tile + t0 * trow;
-        for (int i = lane; i < trow; i += 64) tl[i] = 0;
-        const int s0 = G * ((rho * t0) % T), sc = s0 % Cm, si = s0 / Cm;
+        for (int r = 0; r < nr; ++r)
+            for (int i = lane; i < trow / V; i += 64) ((Wv *)(tl + r * P * trow))[i] = 0;
+        const int s0 = G * ((rho0 * t0) % T), sc = s0 % Cm, si = s0 / Cm;
+        const int s1 = G * (((Q - rho0) * t0) % T);  // (a pair's second)
         int off_k[Q];
 #pragma unroll
         for (int k = 0; k < Q; ++k) off_k[k] = __builtin_amdgcn_readlane(slot, k);
-        for (int l = lane; l < third; l += 64) {
-            const int i1 = l / F, f = l - i1 * F;
-            int c = f0 + f - sc;  // class of the source word
-            const int wrap = c < 0 ? 1 : 0;
-            c += wrap ? Cm : 0;
-            const int e = c + Cm * i1;  // its word in the chunk
-            int row = i1 + wrap + si;   // target row for t1 = 0, of 2 Q
-            row -= row >= Q ? Q : 0;
-            uint32_t *dst = tl + row * F + f;
-            const int at = (t0 * M + e) * 4;
-            uint32_t w[Q];
-#pragma unroll
-            for (int k = 0; k < Q; ++k) w[k] = __builtin_amdgcn_raw_buffer_load_b32(in, at, off_k[k], 0);
-            if (rem) {
-                uint32_t h[Q];
-#pragma unroll
-                for (int k = 0; k < Q; ++k) h[k] = __builtin_amdgcn_raw_buffer_load_b32(in, at + 4, off_k[k], 0);
-#pragma unroll
-                for (int k = 0; k < Q; ++k) w[k] = funnel(h[k], w[k], rem);
+        for (int l = lane * V; l < third; l += 64 * V) {
+            // source word e of the chunks and its target for t1 = 0 (of two
+            // periods, in the first)
+            int e, to;
+            if constexpr (F == Cm) {
+                e = l;
+                to = si * F + sc + l;
+            } else {
+                const int i1 = l / F, f = l - i1 * F;
+                int c = f0 + f - sc;
+                const int wrap = c < 0 ? 1 : 0;
+                c += wrap ? Cm : 0;
+                e = c + Cm * i1;
+                to = (i1 + wrap + si) * F + f;
             }
-            auto scatter = [&](auto d) PA_INLINE {
-                constexpr int DD = decltype(d)::value;
+            to -= to >= period ? period : 0;
+            uint32_t *dst = tl + to, *dst1 = nullptr;
+            if constexpr (R == 2) {
+                to = s1 + l;
+                to -= to >= period ? period : 0;
+                dst1 = tl + P * trow + to;
+            }
+            const int at = (t0 * M + e) * 4;
+            // NB loads in flight a lane (pairs: 9, for the registers)
+            constexpr int NB = V == 2 ? 9 : Q;
 #pragma unroll
-                for (int k = 0; k < Q / DD; ++k) {
-                    uint32_t x = w[k * DD];
+            for (int g = 0; g < Q; g += NB) {
+                Wv w[NB];
+                if (V == 1 || !off) {
 #pragma unroll
-                    for (int b = 1; b < DD; ++b) x ^= w[k * DD + b];
-                    atomicXor(dst + k * (DD * F), x);
+                    for (int k = 0; k < NB; ++k) {
+                        if constexpr (V == 2) w[k] = ld64(in, at, off_k[g + k]);
+                        else w[k] = (Wv)__builtin_amdgcn_raw_buffer_load_b32(in, at, off_k[g + k], 0);
+                    }
+                    if (V == 1 && rem) {
+                        uint32_t h[NB];
+#pragma unroll
+                        for (int k = 0; k < NB; ++k)
+                            h[k] = __builtin_amdgcn_raw_buffer_load_b32(in, at + 4, off_k[g + k], 0);
+#pragma unroll
+                        for (int k = 0; k < NB; ++k) w[k] = funnel(h[k], (uint32_t)w[k], rem);
+                    }
+                } else {
+                    // (pairs of a source that starts inside its buffer)
+#pragma unroll
+                    for (int k = 0; k < NB; ++k) {
+                        const uint32_t a = __builtin_amdgcn_raw_buffer_load_b32(in, at, off_k[g + k], 0),
+                                       b = __builtin_amdgcn_raw_buffer_load_b32(in, at + 4, off_k[g + k], 0),
+                                       c = __builtin_amdgcn_raw_buffer_load_b32(in, at + 8, off_k[g + k], 0);
+                        w[k] = (Wv)((uint64_t)funnel(c, b, rem) << 32 | funnel(b, a, rem));
+                    }
                 }
-            };
-            if (D == 1) scatter(std::integral_constant<int, 1>{});
-            else if (D == 3) scatter(std::integral_constant<int, 3>{});
-            else if (D == 9) scatter(std::integral_constant<int, 9>{});
-            else scatter(std::integral_constant<int, Q>{});
+                auto scatter = [&](auto d) PA_INLINE {
+                    constexpr int DD = decltype(d)::value, C = DD < NB ? DD : NB;
+#pragma unroll
+                    for (int k = 0; k < NB / C; ++k) {
+                        Wv x = w[k * C];
+#pragma unroll
+                        for (int b = 1; b < C; ++b) x ^= w[k * C + b];
+                        atomicXor((Wv *)(dst + (g / DD + k) * (DD * F)), x);
+                        // the other rho's targets go the other way round
+                        if (R == 2 && DD < Q)
+                            atomicXor((Wv *)(dst1 + (Q / DD - g / DD - k) % (Q / DD) * (DD * F)), x);
+                    }
+                };
+                if (D == 1) scatter(std::integral_constant<int, 1>{});
+                else if (D == 3) scatter(std::integral_constant<int, 3>{});
+                else if (D == 9) scatter(std::integral_constant<int, 9>{});
+                else scatter(std::integral_constant<int, Q>{});
+            }
             // take back what lies past the source's last bit: the rest of
-            // its last word and, if words are shifted, the word after
+            // its last word and the word after
 #pragma unroll
             for (int d = 0; d < 2; ++d) {
-                const int W = last + d, t = W / M;
-                if (t % P == t0 && W - t * M == e && t < T) {
+                const int W = last + d, t = W / M, ew = W - t * M - e;
+                if (t % P == t0 && ew >= 0 && ew < V && t < T) {
                     const uint32_t lo = (uint32_t)ld32(in, W * 4), hi = rem ? (uint32_t)ld32(in, W * 4 + 4) : 0u;
                     const uint32_t keep = d ? 0u : ~0u >> (31 - ((nbits - 1) & 31));
-                    atomicXor(dst + rho * (t / P) % Q * F, funnel(hi, lo, rem) & ~keep);
+                    const uint32_t x = funnel(hi, lo, rem) & ~keep;
+                    atomicXor(dst + ew + rho0 * (t / P) % Q * F, x);
+                    if (R == 2 && nr == 2) atomicXor(dst1 + ew + (Q - rho0) * (t / P) % Q * F, x);
                 }
             }
         }
         // to periodic form, two periods
-        for (int l = lane; l < third; l += 64) {
-            const uint32_t a = tl[l] ^ tl[l + period], b = tl[l + third] ^ tl[l + third + period],
-                           c = tl[l + 2 * third] ^ tl[l + 2 * third + period];
-            tl[l] = tl[l + period] = a ^ c;
-            tl[l + third] = tl[l + third + period] = a ^ b;
-            tl[l + 2 * third] = tl[l + 2 * third + period] = b ^ c;
+        for (int r = 0; r < nr; ++r)
+        for (int l = lane; l < third / V; l += 64) {
+            Wv *x = (Wv *)(tl + r * P * trow) + l;
+            constexpr int th = third / V, pe = period / V;
+            const Wv a = x[0] ^ x[pe], b = x[th] ^ x[th + pe], c = x[2 * th] ^ x[2 * th + pe];
+            x[0] = x[pe] = a ^ c;
+            x[th] = x[th + pe] = a ^ b;
+            x[2 * th] = x[2 * th + pe] = b ^ c;
         }
     }
     __syncthreads();
     const rsrc_t xo = make_rsrc(src ? job.S : job.A, (uint32_t)(2 * T * M * 4));
+    for (int r = 0; r < nr; ++r)
     for (int sg = wave; sg < P; sg += kGfWaves) {
+        const int rho = r ? Q - rho0 : rho0;
+        const uint32_t *tr = tile + r * P * trow;
         // tile t0 rotated by (Q / P) sigma t0 rows, as a word offset
         const int turn = lane * trow + (Q - Q / P * sg * lane % Q) * F;
         int off_t[P];
 #pragma unroll
         for (int t0 = 0; t0 < P; ++t0) off_t[t0] = __builtin_amdgcn_readlane(turn, t0);
-        for (int l = lane; l < third; l += 64) {
+        for (int l = lane * V; l < third; l += 64 * V) {
             const int i = l / F, f = l - i * F;
-            uint32_t lo = 0, hi = 0;
+            Wv lo = 0, hi = 0;
 #pragma unroll
             for (int t0 = 0; t0 < P; ++t0) {
-                lo ^= tile[off_t[t0] + l];
-                hi ^= tile[off_t[t0] + l + 2 * third];
+                lo ^= *(const Wv *)(tr + off_t[t0] + l);
+                hi ^= *(const Wv *)(tr + off_t[t0] + l + 2 * third);
             }
             const int at = ((rho + Q * sg) * (2 * M) + i * Cm + f0 + f) * 4;
-            st32(xo, at, (int)lo);
-            st32(xo, at + M * 4, (int)hi);
+            if constexpr (V == 2) {
+                st64(xo, at, lo);
+                st64(xo, at + M * 4, hi);
+            } else {
+                st32(xo, at, (int)lo);
+                st32(xo, at + M * 4, (int)hi);
+            }
         }
     }
 }
@@ -705,8 +768,9 @@ hipError_t launch_gf_parts(const GfChoice &c, const JobArgs &ja, int njobs, hipS
 }
 
 // The forward kernels that exist, by (T, g): the classes per workgroup of
-// launches over many jobs (the widest runs of words that fill the lanes) and
-// of a few jobs (more workgroups).
+// launches over many jobs (whole chunks in order, and two rho a workgroup
+// where its LDS leaves room for another workgroup) and of a few jobs (more
+// workgroups: one block of 10^6 bits 5.7 us, 7.5 with the others).
 struct GfFwdFn {
     int T, g, F;
     bool many;
@@ -714,18 +778,19 @@ struct GfFwdFn {
     unsigned wgs;
     size_t lds;
 };
-template <int Q, int P, int G, int F>
+template <int Q, int P, int G, int F, int R = 1>
 static GfFwdFn gf_fwd_fn(bool many) {
-    return {P * Q, G, F, many, (const void *)k_gf_fwd<Q, P, G, F>, (unsigned)(Q * (G * P / F)),
-            (size_t)P * 2 * Q * F * 4};
+    return {P * Q, G, F, many, (const void *)k_gf_fwd<Q, P, G, F, R>, (unsigned)((R == 2 ? Q / 2 + 1 : Q) * (G * P / F)),
+            (size_t)R * P * 2 * Q * F * 4};
 }
 static const GfFwdFn *gf_fwd_table(int *count) {
     static const GfFwdFn table[] = {
-        gf_fwd_fn<9, 9, 1, 9>(true),      gf_fwd_fn<9, 9, 2, 18>(true),   gf_fwd_fn<9, 9, 3, 27>(true),
-        gf_fwd_fn<27, 9, 1, 9>(true),     gf_fwd_fn<27, 9, 2, 18>(true),  gf_fwd_fn<27, 9, 3, 27>(true),
-        gf_fwd_fn<27, 9, 4, 18>(true),    gf_fwd_fn<27, 9, 5, 15>(true),  gf_fwd_fn<27, 27, 1, 9>(true),
-        gf_fwd_fn<27, 27, 3, 9>(true),    gf_fwd_fn<27, 9, 2, 6>(false),  gf_fwd_fn<27, 9, 3, 9>(false),
-        gf_fwd_fn<27, 9, 4, 6>(false),    gf_fwd_fn<27, 9, 5, 5>(false)};
+        gf_fwd_fn<9, 9, 1, 9, 2>(true),  gf_fwd_fn<9, 9, 2, 18, 2>(true), gf_fwd_fn<9, 9, 3, 27, 2>(true),
+        gf_fwd_fn<27, 9, 1, 9, 2>(true), gf_fwd_fn<27, 9, 2, 18, 2>(true), gf_fwd_fn<27, 9, 3, 27>(true),
+        gf_fwd_fn<27, 9, 4, 36>(true),   gf_fwd_fn<27, 9, 5, 45>(true),  gf_fwd_fn<27, 27, 1, 27>(true),
+        gf_fwd_fn<27, 27, 3, 27>(true),  gf_fwd_fn<27, 9, 1, 3>(false),  gf_fwd_fn<27, 9, 2, 6>(false),
+        gf_fwd_fn<27, 9, 3, 9>(false),   gf_fwd_fn<27, 9, 4, 12>(false), gf_fwd_fn<27, 9, 5, 5>(false),
+        gf_fwd_fn<27, 27, 1, 9>(false),  gf_fwd_fn<27, 27, 3, 9>(false)};
     *count = (int)(sizeof(table) / sizeof(table[0]));
     return table;
 }
