@@ -473,6 +473,15 @@ __global__ void __launch_bounds__(64 * kGfWaves) k_gf_fwd(JobArgs ja) {
 // 2 * 3^a products there are binary Toeplitz products on the matrix cores:
 // with the periodic sequence of one factor, output x is the plain
 // correlation at x for 0 <= x < 64 M2, so no reduction follows.
+//
+// Vector issue and the matrix cores bound it: they hardly overlap (256
+// blocks of 10^6 bits: 850 us, 290 of it without the leaf products, 700 with
+// a fifth of their matrix instructions).  So the leaf loop expands each
+// column window once for all tiles, its outputs go to their places at
+// immediate offsets, and the transforms of both factors run one after the
+// other so that the row operands can take the first one's place: two
+// workgroups a CU up to M2 = 45 (blocks of 2.5 10^6 bits: 427 us for eight
+// with one, 330 with two).
 template <int A, int M2, int W>
 struct GfMul {
     static constexpr int NA = A == 1 ? 3 : A == 2 ? 9 : 27;
@@ -482,16 +491,16 @@ struct GfMul {
     // tiles of one sweep over k (their row fragments stay in registers)
     static constexpr int sweeps = (tiles + 6) / 7, nt = (tiles + sweeps - 1) / sweeps;
     static constexpr int waves = W;
-    // LDS (words): the five-third table of X (then the products), that of S
-    // (then the expanded row operands; two words per 16 bits of 128 M2), and
-    // the reversed column operands (then the inverse transform's output)
+    // LDS (words): area A, the five-third table of X, then the expanded row
+    // operands (two words per 16 bits of 128 M2), then the product; area B,
+    // the table of S, then that of the products; and the reversed column
+    // operands, then the inverse transform's output
     static constexpr int table = (NP * 5 * M2 + 3) / 4 * 4;
     static constexpr int row = 16 * M2, over = 16 * (2 * nt * sweeps + steps);  // a fragment may end past its row
     static constexpr int col = 4 * steps + 2, cols = NP * col > 4 * M ? NP * col : 4 * M;
-    // points whose row operands are in LDS together: all, or those of one r
-    static constexpr int passes = (2 * table + NP * row + over + cols) * 4 <= 80 * 1024 ? 1 : 2;
-    static constexpr int PP = NP / passes;
-    static constexpr int off_s = table, off_row = 2 * table, off_col = off_row + PP * row + over;
+    static constexpr int area = NP * row + over;
+    static_assert(area >= table && area >= 3 * M, "area A");
+    static constexpr int off_b = area, off_col = area + table;
     static constexpr int lds_words = off_col + cols;
 };
 
@@ -503,7 +512,7 @@ __global__ void __launch_bounds__(64 * W) k_gf_mul(JobArgs ja, int T, int g, int
     const int tau = (int)blockIdx.x, tid = threadIdx.x;
     const int lane = tid & 63, wave = (int)uni((uint32_t)tid >> 6);
     uint32_t *lds = (uint32_t *)pa_lds;
-    uint32_t *tx = lds, *ts = lds + G::off_s, *rw = lds + G::off_row, *va = lds + G::off_col;
+    uint32_t *tx = lds, *rw = lds, *ts = lds + G::off_b, *va = lds + G::off_col;
     const int32_t *S = resident ? job.Shat : job.S;
     const rsrc_t xr = make_rsrc(job.A + (size_t)tau * 2 * M, 2 * M * 4);
     const rsrc_t sr = make_rsrc(S + (size_t)tau * 2 * M, 2 * M * 4);
@@ -527,39 +536,54 @@ __global__ void __launch_bounds__(64 * W) k_gf_mul(JobArgs ja, int T, int g, int
         t[3 * M2] = lo ^ hi;
         t[4 * M2] = lo;
     }
-    for (int i = tid; i < NP * G::col; i += NTH) va[i] = 0;
+    // the column operands' words before and after the element
+    for (int i = tid; i < NP * (G::col - 2 * M2); i += NTH) {
+        const int pt = i / (G::col - 2 * M2), j = i - pt * (G::col - 2 * M2);
+        va[pt * G::col + (j ? 2 * M2 + j : 0)] = 0;
+    }
     __syncthreads();
-#pragma unroll 1
-    for (int pass = 0; pass < G::passes; ++pass) {
-    const int first = pass * G::PP;  // the pass's points are first .. first + PP - 1
-    // values at the points u^(3 i + r): sums of coefficients rotated by
-    // (3 i + r) c U
-    for (int tk = tid; tk < 2 * G::PP * M2; tk += NTH) {
-        const bool second = tk >= G::PP * M2;
-        const int k = second ? tk - G::PP * M2 : tk;
-        const int at = k / M2, p0 = k - at * M2, pt = first + at;
+    // value at the point u^(3 i + r), pt = (r - 1) NA + i: the sum of
+    // coefficients rotated by (3 i + r) c U; words p0 of both halves
+    auto value = [&](const uint32_t *t, int pt, int p0, uint32_t &b0, uint32_t &b1) PA_INLINE {
         const int r = pt >= NA ? 2 : 1;
         const uint32_t step = (uint32_t)(U * (3 * (pt - (r - 1) * NA) + r));
-        const uint32_t *t = (second ? ts : tx) + (r - 1) * NA * 5 * M2;
-        uint32_t b0 = 0, b1 = 0, qq = (uint32_t)p0;
+        t += (r - 1) * NA * 5 * M2;
+        uint32_t qq = (uint32_t)p0;
+        b0 = b1 = 0;
 #pragma unroll
-        for (int c = 0; c < NA; ++c) {
-            b0 ^= t[c * 5 * M2 + qq];
-            b1 ^= t[c * 5 * M2 + qq + 2 * M2];
-            qq = sub_mod(qq, step, 3 * M2);
+        for (int c = 0; c < NA; c += 3) {
+            uint32_t w[3][2];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                w[i][0] = t[(c + i) * 5 * M2 + qq];
+                w[i][1] = t[(c + i) * 5 * M2 + qq + 2 * M2];
+                qq = sub_mod(qq, step, 3 * M2);
+            }
+            b0 = xor3(b0, w[0][0], w[1][0]) ^ w[2][0];
+            b1 = xor3(b1, w[0][1], w[1][1]) ^ w[2][1];
         }
-        if (second) {  // the periodic sequence (b0, b0 + b1, b1, b0), expanded
-            gf_v4i *o = (gf_v4i *)(rw + at * G::row) + p0;
-            const gf_v4i e0 = expand_units(b0);
-            o[0] = e0;
-            o[M2] = expand_units(b0 ^ b1);
-            o[2 * M2] = expand_units(b1);
-            o[3 * M2] = e0;
-        } else {  // bit-reversed as a whole, after one word of zeros
-            uint32_t *o = va + pt * G::col;
-            o[2 * M2 - p0] = __builtin_bitreverse32(b0);
-            o[M2 - p0] = __builtin_bitreverse32(b1);
-        }
+    };
+    for (int k = tid; k < NP * M2; k += NTH) {
+        const int pt = k / M2, p0 = k - pt * M2;
+        uint32_t b0, b1;
+        value(tx, pt, p0, b0, b1);
+        // bit-reversed as a whole, after one word of zeros
+        uint32_t *o = va + pt * G::col;
+        o[2 * M2 - p0] = __builtin_bitreverse32(b0);
+        o[M2 - p0] = __builtin_bitreverse32(b1);
+    }
+    __syncthreads();
+    for (int k = tid; k < NP * M2; k += NTH) {
+        const int pt = k / M2, p0 = k - pt * M2;
+        uint32_t b0, b1;
+        value(ts, pt, p0, b0, b1);
+        // the periodic sequence (b0, b0 + b1, b1, b0), expanded
+        gf_v4i *o = (gf_v4i *)(rw + pt * G::row) + p0;
+        const gf_v4i e0 = expand_units(b0), e1 = expand_units(b1);
+        o[0] = e0;
+        o[M2] = e0 ^ e1;
+        o[2 * M2] = e1;
+        o[3 * M2] = e0;
     }
     __syncthreads();
     // leaf products.  out[x] = sum_k row[x + k] col[k - q - 1] over the row
@@ -569,10 +593,13 @@ __global__ void __launch_bounds__(64 * W) k_gf_mul(JobArgs ja, int T, int g, int
     {
         typedef gf_v4i __attribute__((aligned(8))) gf_v4i_a8;
         const int q = lane & 15, kb = lane >> 4;
-        for (int at = wave; at < G::PP; at += G::waves) {
-            const int pt = first + at;
+        // the waves that take one product more are on other SIMDs in other
+        // workgroups
+        static_assert(G::waves % 4 == 0, "waves are spread evenly over the SIMDs");
+        for (int pt = (int)((uint32_t)(wave + (tau & 3)) % (uint32_t)G::waves); pt < NP; pt += G::waves) {
             const uint32_t *cl = va + pt * G::col + kb;
-            const uint32_t *rx = rw + at * G::row + (q + 2 * kb) * 2;
+            const uint32_t *rx = rw + pt * G::row + (q + 2 * kb) * 2;
+            uint32_t *to = ts + pt * 5 * M2;
 #pragma unroll 1
             for (int sw = 0; sw < G::sweeps; ++sw, rx += G::nt * 32) {
                 constexpr int NT = G::nt, ST = G::steps;
@@ -589,42 +616,54 @@ __global__ void __launch_bounds__(64 * W) k_gf_mul(JobArgs ja, int T, int g, int
                         acc[t] = bit_mfma(b, af[k + 2 * t], acc[t]);
                     }
                 }
-                // out halves 0 .. 2 M2 - 1 are the element's high part, then
-                // its low part
+                // output halfwords 0 .. 2 M2 - 1 are the element's high part,
+                // the next 2 M2 its low part: thirds 2 and 3 of the table
+                // (tiles may end in the last third, written below)
+                static_assert(32 * G::sweeps * NT <= 20 * M2 - 8 * M2, "tiles end in the point's table");
                 const uint2 hw = tile_halfwords<NT>(acc);
-                uint16_t *o = (uint16_t *)(tx + pt * 5 * M2);
+                uint16_t *o = (uint16_t *)(to + 2 * M2) + 16 * (sw * NT + 4 * kb) + q;
+                auto put = [&](int i) PA_INLINE { o[16 * i] = (uint16_t)((i & 2 ? hw.y : hw.x) >> (16 * (i & 1))); };
+                constexpr int two = NT > 4 ? NT - 4 : 0;  // fields that lanes 16 .. 31 hold too
+                if (lane < 32) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int t = 4 * kb + i, x = 16 * (sw * NT + t) + q;
-                    if (kb < 2 && t < NT && x < 4 * M2)
-                        o[x < 2 * M2 ? x + 4 * M2 : x - 2 * M2] = (uint16_t)((i & 2 ? hw.y : hw.x) >> (16 * (i & 1)));
+                    for (int i = 0; i < two; ++i) put(i);
+                }
+                if (lane < 16) {
+#pragma unroll
+                    for (int i = two; i < (NT < 4 ? NT : 4); ++i) put(i);
                 }
             }
             __builtin_amdgcn_wave_barrier();
-            for (int x = lane; x < M2; x += 64) {
-                uint32_t *o = tx + pt * 5 * M2 + x;
-                const uint32_t lo = o[0], v = lo ^ o[2 * M2];
+            if (lane < M2) {
+                static_assert(M2 <= 64, "a lane a word");
+                uint32_t *o = to + lane;
+                const uint32_t lo = o[3 * M2], v = lo ^ o[2 * M2];
+                o[0] = lo;
                 o[M2] = v;
-                o[3 * M2] = lo;
                 o[4 * M2] = v;
             }
         }
     }
     __syncthreads();
-    }
     // inverse: coefficient c modulo z^NA - v^(r M2)
     for (int tk = tid; tk < 2 * M; tk += NTH) {
         const int r = tk >= M ? 2 : 1, k = tk - (r - 1) * M;
         const int c = k / M2, p0 = k - c * M2;
-        const uint32_t *t = tx + (r - 1) * NA * 5 * M2;
+        const uint32_t *t = ts + (r - 1) * NA * 5 * M2;
         uint32_t b0 = 0, b1 = 0;
         const uint32_t step = (uint32_t)(3 * U * c);  // < 3 M2, as is U r c
         uint32_t qq = add_mod((uint32_t)p0, (uint32_t)(U * r * c), 3 * M2);
 #pragma unroll
-        for (int i = 0; i < NA; ++i) {
-            b0 ^= t[i * 5 * M2 + qq];
-            b1 ^= t[i * 5 * M2 + qq + 2 * M2];
-            qq = add_mod(qq, step, 3 * M2);
+        for (int i = 0; i < NA; i += 3) {
+            uint32_t w[3][2];
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                w[j][0] = t[(i + j) * 5 * M2 + qq];
+                w[j][1] = t[(i + j) * 5 * M2 + qq + 2 * M2];
+                qq = add_mod(qq, step, 3 * M2);
+            }
+            b0 = xor3(b0, w[0][0], w[1][0]) ^ w[2][0];
+            b1 = xor3(b1, w[0][1], w[1][1]) ^ w[2][1];
         }
         va[tk] = b0;          // [r][c][p0], low halves, then high halves
         va[2 * M + tk] = b1;
@@ -649,9 +688,9 @@ __global__ void __launch_bounds__(64 * W) k_gf_mul(JobArgs ja, int T, int g, int
                 c0 ^= top;
                 c1 ^= hi_of(NA - 1, o) ^ top;
             }
-            ts[p] = c0;
-            ts[M + p] = c0 ^ c1;
-            ts[2 * M + p] = c1;
+            tx[p] = c0;
+            tx[M + p] = c0 ^ c1;
+            tx[2 * M + p] = c1;
         }
     }
     __syncthreads();
@@ -663,7 +702,7 @@ __global__ void __launch_bounds__(64 * W) k_gf_mul(JobArgs ja, int T, int g, int
         for (int p = tid; p < 3 * M; p += NTH) {
             int k = p + d;
             if (k >= 3 * M) k -= 3 * M;
-            const int v = (int)(ts[p] ^ ts[k]);
+            const int v = (int)(tx[p] ^ tx[k]);
             st32(ho, p * 4, v);
             if (p < M) st32(ho, (p + 3 * M) * 4, v);
         }
@@ -770,7 +809,7 @@ hipError_t launch_gf_parts(const GfChoice &c, const JobArgs &ja, int njobs, hipS
 // The forward kernels that exist, by (T, g): the classes per workgroup of
 // launches over many jobs (whole chunks in order, and two rho a workgroup
 // where its LDS leaves room for another workgroup) and of a few jobs (more
-// workgroups: one block of 10^6 bits 5.7 us, 7.5 with the others).
+// workgroups).
 struct GfFwdFn {
     int T, g, F;
     bool many;
