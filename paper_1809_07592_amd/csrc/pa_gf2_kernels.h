@@ -766,6 +766,107 @@ __global__ void __launch_bounds__(64 * kGfWaves) k_gf_inv(JobArgs ja, int g) {
     }
 }
 
+// P3 for launches over many jobs.  There the reads of k_gf_inv bound it: every
+// output word reads one word of each of the T products, through L2 (256
+// blocks of 10^6 bits: 1.6 GB in 165 us).  Here a workgroup accumulates
+// 1024 K V consecutive words in registers and the products pass through
+// LDS, nine at a time and once each, so that a word read from memory serves
+// as many outputs as the workgroup has rows of 3 M words (17 at that size);
+// word pairs for even G, whose rotations keep them.  Bound by the LDS reads
+// and the three operations that step an offset modulo 3 M.
+// Grid: (ranges of 1024 K V - 2 output words, jobs), 16 waves.
+template <int T, int G, int K>
+struct GfInvMany {
+    static constexpr int M = T / 3 * G, V = G % 2 == 0 ? 2 : 1, NTH = 1024;
+    static constexpr int cover = NTH * K * V, step = cover - 2;  // words held, words written
+    static constexpr int stage = 9 * 3 * M;                     // words of nine products
+    static constexpr size_t lds = (size_t)(2 * stage > cover ? 2 * stage : cover) * 4;
+};
+template <int T, int G, int K>
+__global__ void __launch_bounds__(1024) k_gf_inv_many(JobArgs ja) {
+    using I = GfInvMany<T, G, K>;
+    constexpr int M = I::M, V = I::V, NTH = I::NTH, PE = 3 * M, NL = (9 * PE / V + NTH - 1) / NTH;
+    static_assert(T % 9 == 0 && PE % V == 0, "nine products a stage");
+    typedef typename std::conditional<V == 2, unsigned long long, uint32_t>::type Wv;
+    const JobDesc job = job_of(ja, uni(blockIdx.y));
+    const int tid = threadIdx.x;
+    const int words = (int)((job.m + 63u) / 64u * 2u), W0 = (int)((job.n - 1u) / 32u);
+    // cyclic word of the range's first (V = 2: even, so that pairs lie in a row)
+    const int base = (W0 & ~(V - 1)) + (int)blockIdx.x * I::step;
+    if (base - W0 >= words) return;
+    const rsrc_t h = make_rsrc(job.A + (size_t)T * 2 * M, (uint32_t)(T * 4 * M * 4));
+    uint32_t *lds = (uint32_t *)pa_lds;
+    uint32_t at[K], step[K];  // bytes: offset in the next product, and what the following ones add
+    Wv acc[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        int W = base + (tid + NTH * k) * V;
+        W -= W >= T * M ? T * M : 0;
+        W = W < T * M ? W : 0;  // (words past the last output)
+        const int t = W / M;
+        at[k] = (uint32_t)(W - t * M) * 4;
+        step[k] = (uint32_t)(G * t) * 4;
+        acc[k] = 0;
+    }
+    Wv w[NL];
+    auto load = [&](int c) PA_INLINE {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int f = (tid + NTH * i) * V, r = f / PE;
+            const int o = (r * 4 * M + f - r * PE) * 4;
+            if ((i + 1) * NTH * V <= 9 * PE || f < 9 * PE) {
+                if constexpr (V == 2) w[i] = ld64(h, o, c * (9 * 4 * M * 4));
+                else w[i] = (Wv)__builtin_amdgcn_raw_buffer_load_b32(h, o, c * (9 * 4 * M * 4), 0);
+            }
+        }
+    };
+    auto store = [&](int buf) PA_INLINE {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int f = (tid + NTH * i) * V;
+            if ((i + 1) * NTH * V <= 9 * PE || f < 9 * PE) *(Wv *)(lds + buf * I::stage + f) = w[i];
+        }
+    };
+    auto add = [&](int buf) PA_INLINE {
+        const char *b = (const char *)(lds + buf * I::stage);
+#pragma unroll
+        for (int r = 0; r < 9; ++r)
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                acc[k] ^= *(const Wv *)(b + at[k] + r * (PE * 4));
+                at[k] = add_mod(at[k], step[k], (uint32_t)(PE * 4));
+            }
+    };
+    load(0);
+    store(0);
+    __syncthreads();
+    // products 9 c .. 9 c + 8 in buffer c & 1; the next nine are loaded meanwhile
+#pragma unroll 1
+    for (int c = 0; c < T / 9; c += 2) {
+        if (c + 1 < T / 9) load(c + 1);
+        add(0);
+        if (c + 1 < T / 9) {
+            store(1);
+            __syncthreads();
+            if (c + 2 < T / 9) load(c + 2);
+            add(1);
+            if (c + 2 < T / 9) store(0);
+        }
+        __syncthreads();
+    }
+    // the output starts at bit n - 1 of the product: each word takes bits of
+    // the next one too
+#pragma unroll
+    for (int k = 0; k < K; ++k) *(Wv *)(lds + (tid + NTH * k) * V) = acc[k];
+    __syncthreads();
+    const OutWords out(job);
+    const uint32_t sh = (job.n - 1u) & 31u;
+    for (int f = tid; f < I::step; f += NTH) {
+        const int w = base + f - W0;
+        if (w >= 0 && w < words) out.put((uint32_t)w, funnel(lds[f + 1], lds[f], sh));
+    }
+}
+
 // ---------------------------------------------------------------- launchers
 
 static hipError_t set_lds_limits(int *limit);  // once per device, with gf_set_lds_limits
@@ -873,6 +974,27 @@ static const GfMulFn *gf_mul_table(int *count) {
     return table;
 }
 
+// The inverse kernels for many jobs: K ascending.
+struct GfInvFn {
+    int T, g, step;
+    const void *fn;
+    size_t lds;
+};
+template <int T, int G, int K>
+static GfInvFn gf_inv_fn() {
+    using I = GfInvMany<T, G, K>;
+    return {T, G, I::step, (const void *)k_gf_inv_many<T, G, K>, I::lds};
+}
+static const GfInvFn *gf_inv_table(int *count) {
+    static const GfInvFn table[] = {
+        gf_inv_fn<243, 1, 1>(), gf_inv_fn<243, 1, 2>(), gf_inv_fn<243, 1, 4>(), gf_inv_fn<243, 2, 1>(),
+        gf_inv_fn<243, 2, 2>(), gf_inv_fn<243, 2, 4>(), gf_inv_fn<243, 3, 1>(), gf_inv_fn<243, 3, 2>(),
+        gf_inv_fn<243, 3, 4>(), gf_inv_fn<243, 4, 1>(), gf_inv_fn<243, 4, 2>(), gf_inv_fn<243, 4, 4>(),
+        gf_inv_fn<243, 5, 1>(), gf_inv_fn<243, 5, 2>(), gf_inv_fn<243, 5, 4>()};
+    *count = (int)(sizeof(table) / sizeof(table[0]));
+    return table;
+}
+
 // Kernels whose workgroups use more than the default LDS.
 static hipError_t gf_set_lds_limits(int maxb) {
     int n = 0;
@@ -883,6 +1005,9 @@ static hipError_t gf_set_lds_limits(int maxb) {
     const GfFwdFn *f = gf_fwd_table(&n);
     for (int i = 0; i < n && e == hipSuccess; ++i)
         e = hipFuncSetAttribute(f[i].fn, hipFuncAttributeMaxDynamicSharedMemorySize, maxb);
+    const GfInvFn *v = gf_inv_table(&n);
+    for (int i = 0; i < n && e == hipSuccess; ++i)
+        e = hipFuncSetAttribute(v[i].fn, hipFuncAttributeMaxDynamicSharedMemorySize, maxb);
     return e;
 }
 
@@ -899,12 +1024,26 @@ hipError_t launch_gf_mul(const GfChoice &c, bool resident, const JobArgs &ja, in
     return gf_launch(best->fn, dim3((unsigned)T, (unsigned)njobs), best->threads, args, best->lds, s, e0, e1);
 }
 
+// Ranges of `step` words that hold a job's output words and one before.
+static unsigned inv_ranges(const GfChoice &c, int step) {
+    return ((c.max_m + 63) / 64 * 2 + 1 + (unsigned)step - 1) / (unsigned)step;
+}
+
 hipError_t launch_gf_inv(const GfChoice &c, const JobArgs &ja, int njobs, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     const void *fn = nullptr;
     if (c.T == 81) fn = (const void *)k_gf_inv<81>;
     if (c.T == 243) fn = (const void *)k_gf_inv<243>;
     if (c.T == 729) fn = (const void *)k_gf_inv<729>;
     if (c.form != kGfSplit || ja.seg) return hipErrorInvalidConfiguration;
+    // many jobs: the widest ranges that still give every CU a workgroup
+    int n = 0;
+    const GfInvFn *v = gf_inv_table(&n), *best = nullptr;
+    for (int i = 0; i < n; ++i)
+        if (v[i].T == c.T && v[i].g == c.g && (uint64_t)inv_ranges(c, v[i].step) * (uint64_t)njobs >= 256) best = &v[i];
+    if (best) {
+        void *many[] = {(void *)&ja};
+        return gf_launch(best->fn, dim3(inv_ranges(c, best->step), (unsigned)njobs), 1024, many, best->lds, s, e0, e1);
+    }
     int g = c.g;
     void *args[] = {(void *)&ja, (void *)&g};
     // output words can begin anywhere in a row of M
