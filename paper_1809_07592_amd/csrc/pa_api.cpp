@@ -705,7 +705,7 @@ pa_status pa_modified_toeplitz_hash(const uint64_t *key_bits, uint64_t n, const 
     hipStream_t s = (hipStream_t)stream;
     pa::PlanRef p{};
     PA_TRY(plan_for(L, 0, &p));
-    if (gf_allowed(p)) p.gf = pa::gf_plain_for(n - m, m, pa::required_len(n - m, m), UINT64_MAX, 1);
+    if (gf_allowed(p)) p.gf = pa::gf_plain_for(n - m, m, pa::required_len(n - m + pa::kGfLead, m), UINT64_MAX, 1);
     const uint64_t wa = area_words_a(p), wsd = area_words_s(p);
     void *ws = nullptr;
     std::unique_lock<std::mutex> ws_hold;
@@ -797,15 +797,16 @@ pa_status prepare_batch(const pa_block *blocks, uint32_t count, bool modified, B
         gr.members = g.second;
         PA_TRY(plan_for(g.first, g.second.size() > 1 ? 1 : 0, &gr.plan));
         if (form == kFormLanes && gf_allowed(gr.plan)) {
+            const uint64_t lead = modified ? pa::kGfLead : 0;
             uint64_t n = 0, m = 0, bits = 0;
             for (uint32_t i : gr.members) {
                 const uint64_t kn = modified ? blocks[i].n - blocks[i].m : blocks[i].n;
                 n = std::max(n, kn);
                 m = std::max(m, blocks[i].m);
-                bits = std::max(bits, pa::required_len(kn, blocks[i].m));
+                bits = std::max(bits, pa::required_len(kn + lead, blocks[i].m));
             }
             // a graph's launches keep room for the longest blocks of the length
-            gr.plan.gf = pa::gf_plain_for(n, m, any_sizes ? gr.L : bits, UINT64_MAX, (int)gr.members.size());
+            gr.plan.gf = pa::gf_plain_for(n, m, any_sizes ? gr.L + lead : bits, UINT64_MAX, (int)gr.members.size());
             if (any_sizes) gr.plan.gf.max_m = (uint32_t)(modified ? gr.L : gr.L / 2 + 64);
         }
         if (form == kFormLanes) {

@@ -41,6 +41,10 @@ struct GfChoice {
     uint64_t work_words() const { return 6ull * T * chunk_words(); }          // X, then the products (4 T M)
 };
 
+// Bits by which the split form's product can be shifted: a key that starts
+// inside its buffer (modified Toeplitz) is taken from a whole 64-bit word on.
+constexpr uint64_t kGfLead = 63;
+
 // Split of a cyclic product of at least `bits` bits whose work area fits in
 // `words` 32-bit words; form kGfNone if there is none.
 GfChoice gf_split_for(uint64_t bits, uint64_t words);

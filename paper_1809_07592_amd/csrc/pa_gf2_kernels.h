@@ -288,6 +288,9 @@ __device__ __forceinline__ uint32_t add_mod(uint32_t a, uint32_t b, uint32_t n) 
 // before the barrier.
 constexpr int kGfWaves = 9;
 
+// Bits before the source in its first 64-bit word.
+__device__ __forceinline__ uint32_t gf_lead_bits(const JobDesc &job, bool src) { return src ? 0u : job.key_off & 63u; }
+
 template <int Q, int P, int G, int F, int R>
 __global__ void __launch_bounds__(64 * kGfWaves) k_gf_fwd(JobArgs ja) {
     constexpr int T = P * Q, Q3 = Q / 3, M = T / 3 * G, Cm = G * P, NF = Cm / F;
@@ -306,13 +309,13 @@ __global__ void __launch_bounds__(64 * kGfWaves) k_gf_fwd(JobArgs ja) {
     uint32_t *tile = (uint32_t *)pa_lds;    // [R][P][2 Q][F]
     const int lane = threadIdx.x & 63, wave = (int)uni(threadIdx.x >> 6);
 
-    // word W of the source is bits [32 W, 32 W + 32) from bit `off` of the
-    // buffer, `rem` of its first word; a source that starts at bit 0 is
-    // whole 64-bit words
-    const int nbits = (int)(src ? job.seed_bits : job.n);
-    const uint32_t off = src ? 0u : job.key_off, rem = off & 31u;
-    const rsrc_t in = make_rsrc((const uint32_t *)(src ? job.seed : job.key) + (off >> 5),
-                                off ? (rem + (uint32_t)nbits + 31) / 32 * 4 : ((uint32_t)nbits + 63) / 64 * 8);
+    // A source that starts at bit `off` of its buffer is taken from the
+    // 64-bit word of that bit on, with the `rem` bits before it as zeros: the
+    // product is then shifted by rem, which the inverse pass allows for.  The
+    // words before and after the source are whole 64-bit words of its buffer.
+    const uint32_t off = src ? 0u : job.key_off;
+    const int rem = (int)gf_lead_bits(job, src), nbits = (int)(src ? job.seed_bits : job.n) + rem;
+    const rsrc_t in = make_rsrc((src ? job.seed : job.key) + (off >> 6), ((uint32_t)nbits + 63) / 64 * 8);
     const int last = (nbits - 1) >> 5;
 
     // the Q chunks of a tile in the order of their targets: slot k D + b is
@@ -367,29 +370,10 @@ __global__ void __launch_bounds__(64 * kGfWaves) k_gf_fwd(JobArgs ja) {
 #pragma unroll
             for (int g = 0; g < Q; g += NB) {
                 Wv w[NB];
-                if (V == 1 || !off) {
 #pragma unroll
-                    for (int k = 0; k < NB; ++k) {
-                        if constexpr (V == 2) w[k] = ld64(in, at, off_k[g + k]);
-                        else w[k] = (Wv)__builtin_amdgcn_raw_buffer_load_b32(in, at, off_k[g + k], 0);
-                    }
-                    if (V == 1 && rem) {
-                        uint32_t h[NB];
-#pragma unroll
-                        for (int k = 0; k < NB; ++k)
-                            h[k] = __builtin_amdgcn_raw_buffer_load_b32(in, at + 4, off_k[g + k], 0);
-#pragma unroll
-                        for (int k = 0; k < NB; ++k) w[k] = funnel(h[k], (uint32_t)w[k], rem);
-                    }
-                } else {
-                    // (pairs of a source that starts inside its buffer)
-#pragma unroll
-                    for (int k = 0; k < NB; ++k) {
-                        const uint32_t a = __builtin_amdgcn_raw_buffer_load_b32(in, at, off_k[g + k], 0),
-                                       b = __builtin_amdgcn_raw_buffer_load_b32(in, at + 4, off_k[g + k], 0),
-                                       c = __builtin_amdgcn_raw_buffer_load_b32(in, at + 8, off_k[g + k], 0);
-                        w[k] = (Wv)((uint64_t)funnel(c, b, rem) << 32 | funnel(b, a, rem));
-                    }
+                for (int k = 0; k < NB; ++k) {
+                    if constexpr (V == 2) w[k] = ld64(in, at, off_k[g + k]);
+                    else w[k] = (Wv)__builtin_amdgcn_raw_buffer_load_b32(in, at, off_k[g + k], 0);
                 }
                 auto scatter = [&](auto d) PA_INLINE {
                     constexpr int DD = decltype(d)::value, C = DD < NB ? DD : NB;
@@ -409,15 +393,16 @@ __global__ void __launch_bounds__(64 * kGfWaves) k_gf_fwd(JobArgs ja) {
                 else if (D == 9) scatter(std::integral_constant<int, 9>{});
                 else scatter(std::integral_constant<int, Q>{});
             }
-            // take back what lies past the source's last bit: the rest of
-            // its last word and the word after
+            // take back what lies past the source's last bit (the rest of its
+            // last word and the word after) and before its first
 #pragma unroll
-            for (int d = 0; d < 2; ++d) {
-                const int W = last + d, t = W / M, ew = W - t * M - e;
+            for (int d = 0; d < 4; ++d) {
+                const int W = d < 2 ? last + d : d - 2, t = W / M, ew = W - t * M - e;
+                if (d >= 2 && 32 * (d - 2) >= rem) break;
                 if (t % P == t0 && ew >= 0 && ew < V && t < T) {
-                    const uint32_t lo = (uint32_t)ld32(in, W * 4), hi = rem ? (uint32_t)ld32(in, W * 4 + 4) : 0u;
-                    const uint32_t keep = d ? 0u : ~0u >> (31 - ((nbits - 1) & 31));
-                    const uint32_t x = funnel(hi, lo, rem) & ~keep;
+                    const uint32_t tail = d ? ~0u : ~(~0u >> (31 - ((nbits - 1) & 31)));
+                    const uint32_t head = rem >= 32 * (d - 1) ? ~0u : (1u << (rem & 31)) - 1u;
+                    const uint32_t x = (uint32_t)ld32(in, W * 4) & (d < 2 ? tail : head);
                     atomicXor(dst + ew + rho0 * (t / P) % Q * F, x);
                     if (R == 2 && nr == 2) atomicXor(dst1 + ew + (Q - rho0) * (t / P) % Q * F, x);
                 }
@@ -714,9 +699,10 @@ __global__ void __launch_bounds__(64 * W) k_gf_mul(JobArgs ja, int T, int g, int
 // that e needs no wrap).  A workgroup takes 64 consecutive words of one t
 // from word 63 s; its waves share tau, and each lane finds one product's
 // offset, which the loads take as a scalar.  The output starts at bit
-// n - 1, so each word also takes bits of the next one and 64 words give 63;
-// in a row's last segment the word after the row belongs to t + 1, and the
-// offsets are formed by lane.  The reads (L2) bound it.
+// n - 1 (further on by the bits before the key in its first word), so each
+// word also takes bits of the next one and 64 words give 63; in a row's last
+// segment the word after the row belongs to t + 1, and the offsets are formed
+// by lane.  The reads (address units, 88% busy with many blocks) bound it.
 // Grid: (segments of 63 words of each t that the output can meet, jobs).
 template <int T>
 __global__ void __launch_bounds__(64 * kGfWaves) k_gf_inv(JobArgs ja, int g) {
@@ -724,7 +710,8 @@ __global__ void __launch_bounds__(64 * kGfWaves) k_gf_inv(JobArgs ja, int g) {
     constexpr int K = T / kGfWaves;
     const JobDesc job = job_of(ja, uni(blockIdx.y));
     const int M = T / 3 * g, segs = (M + 62) / 63;
-    const int words = (int)((job.m + 63u) / 64u * 2u), W0 = (int)((job.n - 1u) / 32u);
+    const uint32_t start = job.n + gf_lead_bits(job, false) - 1u;  // bit of the product where the output starts
+    const int words = (int)((job.m + 63u) / 64u * 2u), W0 = (int)(start / 32u);
     const int row = (int)blockIdx.x / segs, t = W0 / M + row, e0 = ((int)blockIdx.x - row * segs) * 63;
     const int w0 = t * M + e0 - W0;  // output word of lane 0
     if (w0 >= words || w0 + 63 <= 0 || t >= T) return;
@@ -762,7 +749,7 @@ __global__ void __launch_bounds__(64 * kGfWaves) k_gf_inv(JobArgs ja, int g) {
         __builtin_amdgcn_wave_barrier();
         const int w = w0 + lane;
         if (lane < 63 && e0 + lane < M && w >= 0 && w < words)
-            OutWords(job).put((uint32_t)w, funnel(red[0][lane + 1], acc, (job.n - 1u) & 31u));
+            OutWords(job).put((uint32_t)w, funnel(red[0][lane + 1], acc, start & 31u));
     }
 }
 
@@ -790,7 +777,8 @@ __global__ void __launch_bounds__(1024) k_gf_inv_many(JobArgs ja) {
     typedef typename std::conditional<V == 2, unsigned long long, uint32_t>::type Wv;
     const JobDesc job = job_of(ja, uni(blockIdx.y));
     const int tid = threadIdx.x;
-    const int words = (int)((job.m + 63u) / 64u * 2u), W0 = (int)((job.n - 1u) / 32u);
+    const uint32_t first = job.n + gf_lead_bits(job, false) - 1u;  // bit of the product where the output starts
+    const int words = (int)((job.m + 63u) / 64u * 2u), W0 = (int)(first / 32u);
     // cyclic word of the range's first (V = 2: even, so that pairs lie in a row)
     const int base = (W0 & ~(V - 1)) + (int)blockIdx.x * I::step;
     if (base - W0 >= words) return;
@@ -860,7 +848,7 @@ __global__ void __launch_bounds__(1024) k_gf_inv_many(JobArgs ja) {
     for (int k = 0; k < K; ++k) *(Wv *)(lds + (tid + NTH * k) * V) = acc[k];
     __syncthreads();
     const OutWords out(job);
-    const uint32_t sh = (job.n - 1u) & 31u;
+    const uint32_t sh = first & 31u;
     for (int f = tid; f < I::step; f += NTH) {
         const int w = base + f - W0;
         if (w >= 0 && w < words) out.put((uint32_t)w, funnel(lds[f + 1], lds[f], sh));
@@ -886,12 +874,12 @@ hipError_t launch_gf_direct(const GfChoice &c, const JobArgs &ja, int njobs, hip
                             hipEvent_t e1) {
     const void *fn = nullptr;
     const bool parts = c.slices > 1;
-    int nw = 8;
-    // few workgroups: 16 waves that share the key in finer chunks
-    if (c.nt == 1) nw = 16, fn = parts ? (const void *)k_gf_direct<1, 8, 16, true> : (const void *)k_gf_direct<1, 8, 16, false>;
-    if (c.nt == 2) nw = 16, fn = parts ? (const void *)k_gf_direct<2, 8, 16, true> : (const void *)k_gf_direct<2, 8, 16, false>;
+    // few tiles a workgroup, so few workgroups: 16 waves that share the key
+    // in finer chunks
+    const int nw = c.nt == 4 ? 8 : 16;
+    if (c.nt == 1 && !parts) fn = (const void *)k_gf_direct<1, 8, 16, false>;
+    if (c.nt == 2 && !parts) fn = (const void *)k_gf_direct<2, 8, 16, false>;
     if (c.nt == 4) fn = parts ? (const void *)k_gf_direct<4, 16, 8, true> : (const void *)k_gf_direct<4, 16, 8, false>;
-    if (c.nt == 8) fn = parts ? (const void *)k_gf_direct<8, 16, 8, true> : (const void *)k_gf_direct<8, 16, 8, false>;
     if (c.form != kGfDirect || ja.seg || c.slices < 1) return hipErrorInvalidConfiguration;
     void *args[] = {(void *)&ja};
     const uint32_t per = 256u * (uint32_t)c.nt;

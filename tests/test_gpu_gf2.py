@@ -79,7 +79,7 @@ def test_direct_every_alignment(modified):
 
 
 @pytest.mark.parametrize("n,m", [(1, 1), (64, 64), (4097, 4097), (70_001, 1), (65_000, 255), (65_001, 256), (65_002, 257),
-                                 (99_991, 1023), (99_999, 1025), (200_017, 30_011), (131_090, 65_535)])
+                                 (99_991, 1023), (99_999, 1025), (200_017, 30_011), (131_090, 65_535), (100_003, 70_001)])
 def test_direct_one_block(n, m):
     check_one(n, m)
     if m < n:
@@ -175,3 +175,53 @@ def test_graph_update_to_other_sizes_of_the_same_lengths():
                 torch.cuda.synchronize()
                 for (k, s, n, m), b in zip(d, blocks):
                     assert np.array_equal(b[4].cpu().numpy().view(np.uint64), oracle.toeplitz_hash(k, n, s, m)), (n, m)
+
+
+def check_many(n, m, jobs, modified=False):
+    """`jobs` blocks, two different ones in turn, each in buffers of its own."""
+    pair = [(*inputs(n, m, modified, tag=t),) for t in range(2)]
+    wants = [want(k, n, s, m, modified) for k, s in pair]
+    sent = [(dev(k), dev(s)) for k, s in pair]
+    out = torch.full((jobs, wl.words(m)), -1, dtype=torch.int64, device="cuda")
+    blocks = [(sent[i % 2][0].clone(), n, sent[i % 2][1].clone(), m, out[i]) for i in range(jobs)]
+    (pa.modified_toeplitz_hash_batched if modified else pa.toeplitz_hash_batched)(blocks)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy().view(np.uint64)
+    bad = [i for i in range(jobs) if not np.array_equal(got[i], wants[i % 2])]
+    assert not bad, (n, m, jobs, modified, bad[:5])
+
+
+@pytest.mark.parametrize("n,m,jobs", [(20_003, 2_001, 40), (9_001, 2_300, 100), (150_001, 3_001, 8)])
+def test_direct_many_blocks(n, m, jobs):
+    # two and four tiles a workgroup, and slices of the key
+    check_many(n, m, jobs)
+
+
+@pytest.mark.parametrize("wide", [1, 2, 4])
+@pytest.mark.parametrize("g", [1, 2, 3, 4, 5])
+def test_split_many_blocks(g, wide):
+    # enough blocks for the inverse pass that stages products, at each of its
+    # widths: ranges of 1024 words (2048 with even g) times 1, 2 and 4
+    half = 16 * 243 * 81 * g - 100
+    cover = 1024 * wide * (2 if g % 2 == 0 else 1) - 2
+    ranges = -(-(-(-half // 64) * 2 + 1) // cover)
+    check_many(half + 37, half - 30, -(-256 // ranges))
+
+
+@pytest.mark.parametrize("n,m,jobs", [(36_001, 33_003, 6), (70_001, 66_003, 6), (104_001, 100_003, 6),
+                                      (3_600_001, 20_003, 5), (5_800_001, 20_003, 5)])
+def test_split_some_blocks(n, m, jobs):
+    check_many(n, m, jobs)
+
+
+@pytest.mark.parametrize("m", [64_000, 64_001, 64_031, 64_032, 64_033, 64_063])
+def test_split_key_inside_its_buffer(m):
+    # every kind of start of the hashed part within its 64-bit word, odd and
+    # even word units, few and many blocks, and a cyclic length that only
+    # the block without those bits would fit
+    for n in (400_001, 900_001):
+        check_one(n, m, modified=True)
+        check_many(n, m, 6, modified=True)
+    total = 32 * 243 * 81
+    check_one(total - 63, m, modified=True)
+    check_many(total - 40, m, 70, modified=True)
