@@ -358,12 +358,16 @@ GfChoice gf_split_for(uint64_t bits, uint64_t words) {
     return GfChoice{};
 }
 
-// Direct up to where the split form is faster.  Measured (us, one block, back
-// to back): n = 200,000 to 50,000 direct 11.5, split 15; 262,144 to 65,536
-// 13.4 and 15; 300,000 to 60,000 15.0 and 15.  Many blocks: 32 of 100,000 to
-// 20,000 34.6 and 33.8, 32 of 200,000 to 40,000 83 and 94; from 10^6 bits the
-// split form takes 4 us a block, where the direct one takes 0.5 us for each
-// 10^9 products.
+// Direct up to where the split form is faster.  One block, back to back (us):
+// n = 200,000 to 50,000 direct 11.5, split 15; 262,144 to 65,536 12.1 and 15;
+// 300,000 to 60,000 15 and 15.  Several blocks cost the direct form about
+// 0.35 us for each 10^9 products and the split form 0.55 us a block at 1.4
+// 10^5 cyclic bits, 2.2 at 6.3 10^5 and 4 at 1.26 10^6, so the line is near
+// 10^4 products for a cyclic bit; with fewer than 32 long blocks the direct
+// form's chains along the key are too long as well (replays of 32 blocks:
+// 70,000 to 20,000 direct 28, split 33; 100,000 to 20,000 36 and 33; 100,000
+// to 50,000 70 and 46; of 8 blocks of 100,000 to 50,000 27 and 24, of
+// 200,000 to 40,000 55 and 35).
 //
 // Tiles a workgroup, and slices of the key: up to 2^17 key bits one launch
 // is faster than two (100,003 to 50,001: 9.1 against 9.7 with slices), with
@@ -377,7 +381,7 @@ GfChoice gf_plain_for(uint64_t n, uint64_t m, uint64_t bits, uint64_t words, int
     split.max_m = (uint32_t)m;
     const double products = (double)n * (double)m;
     double most = 1.75e10;
-    if (njobs > 1 && split.form == kGfSplit) most = std::min(8.0e9, 1.2e4 * (double)split.cyclic_bits());
+    if (njobs > 1 && split.form == kGfSplit) most = std::min(4.0e9, 1.2e4 * (double)split.cyclic_bits());
     if (products > most) return split;
     GfChoice c;
     c.form = kGfDirect;
