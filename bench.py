@@ -3,11 +3,12 @@
 Default workload (the value line): one privacy-amplification block at the
 finite-size scale, n = 10^6 key bits, m = 250,000 output bits, i.i.d.
 Bernoulli(0.5) key and seed bits (seeded, synthetic), plain path: each step
-is one pa_toeplitz_hash call = seed and key column transforms, the fused
-row pass (both row transforms, product, inverse), and the inverse column
-pass with parity extraction.  Inputs are resident in HBM before timing.
-The library's autotuner picks the four-step split per batch class before
-the timed regions (--no-tune keeps the defaults).
+is one pa_toeplitz_hash call = forward transforms of the key and the seed,
+their products ring by ring, and the inverse transform to packed bits.
+Inputs are resident in HBM before timing.  The library's autotuner times
+the carry-less form of the default geometry against the number-theoretic
+transform's four-step splits, per batch class, before the timed regions
+(--no-tune keeps the defaults).
 
 Also reported on the same JSON line:
   * batched: 256 blocks of the same shape in one pa_toeplitz_hash_batched
@@ -33,7 +34,7 @@ Also reported on the same JSON line:
     every served result compared with the same request run alone;
   * roofline of the dominant kernel, from HIP events the library records
     with each launch on its own stream, over a repeat of the timed steps
-    (algorithmic bytes and fp64 operations per launch / average duration);
+    (algorithmic bytes and operations per launch / average duration);
   * parity: the timed outputs of the headline block, the small and the
     large block, every block of the 256-block batch, every 16th of the
     shared-seed batch and every 8th of the uneven batch, compared word for
@@ -58,6 +59,9 @@ if ROOT not in sys.path:
 METRIC = "PA input Gb/s at n=10^6 plain vs batched; p50/p99 latency of serving loop"
 HBM_PEAK_GBS = 8000.0                          # MI355X HBM3E, vendor figure
 FP64_VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12  # CUs x SIMDs x lanes x clock: fp64 FMA/add issue rate
+# binary products on the matrix cores: a 16 x 16 x 128 fp4 instruction (two
+# operations a product) in 16 clocks on each SIMD
+BIT_MFMA_PEAK_TOPS = 256 * 4 * 2 * 16 * 16 * 128 / 16 * 2.4e9 / 1e12
 N_BITS, M_BITS = 1_000_000, 250_000
 
 
@@ -67,7 +71,7 @@ def progress(msg: str) -> None:
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("pa_kernels.hip", "pa_internal.h"):
+    for f in ("pa_kernels.hip", "pa_internal.h", "pa_gf2_kernels.h", "pa_gf2.h"):
         with open(os.path.join(ROOT, "paper_1809_07592_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -102,21 +106,28 @@ def geometry_in_effect(pa, L: int, batch_class: int) -> list:
     return [g["log2_rows"], g["tile_width"], g["row_first"], g["row_threads"]]
 
 
-def kernel_figures(prof: dict, workload: str, geometry=None) -> dict:
+def kernel_figures(prof: dict, workload: str, geometry=None, L: int = 0, blocks: int = 1) -> dict:
     """Per-pass figures from the library's profiler (HIP events recorded by
-    each launch on its stream): average duration, algorithmic bytes and fp64
-    operations per launch, and their fractions of the HBM and fp64 peaks;
-    the measured traffic of the committed counter profile when it was taken
-    on the same kernels in the same geometry."""
+    each launch on its stream): average duration, algorithmic bytes and
+    operations per launch, and their fractions of the HBM and arithmetic
+    peaks; the measured traffic of the committed counter profile when it was
+    taken on the same kernels in the same geometry.  The operations are
+    those of the form that ran: fp64 ones of the number-theoretic passes
+    (whose row pass moves 12 L bytes a block), else binary products on the
+    matrix cores ("rowconv", "direct") and 32-bit sums."""
     out = {}
+    ntt = "rowconv" in prof and prof["rowconv"]["alg_bytes"] / prof["rowconv"]["launches"] >= 12.0 * L * blocks > 0
     for name, st in prof.items():
         avg_s = st["avg_ms"] * 1e-3
         b = st["alg_bytes"] / st["launches"]
         o = st["alg_ops"] / st["launches"]
         t = load_traffic(name, workload, geometry)
+        matrix = not ntt and name in ("rowconv", "direct")
+        peak = BIT_MFMA_PEAK_TOPS if matrix else FP64_VALU_PEAK_TOPS
         out[name] = {"avg_us": st["avg_ms"] * 1e3, "launches": st["launches"], "alg_bytes_per_launch": b,
                      "alg_ops_per_launch": o, "hbm_GBs": b / avg_s / 1e9, "hbm_frac": b / avg_s / 1e9 / HBM_PEAK_GBS,
-                     "fp64_Tops": o / avg_s / 1e12, "alu_frac": o / avg_s / 1e12 / FP64_VALU_PEAK_TOPS,
+                     "ops": "fp64 FMA/add" if ntt else "binary multiply/add" if matrix else "32-bit add",
+                     "Tops": o / avg_s / 1e12, "Tops_peak": peak, "alu_frac": o / avg_s / 1e12 / peak,
                      "traffic": t, "traffic_over_alg": None if t is None else t / b}
     return out
 
@@ -299,7 +310,7 @@ def large_block_run(pa, wl, torch, np, stream, steps, tune):
     g = pa.plan_info(L, *pa.tune_get(L, 0))
     res = {"value": n / (ms * 1e-3) / 1e9, "unit": "Gb/s", "ms_per_block": ms, "n": n, "m": m, "transform_len": L,
            "rows": g["rows"], "cols": g["cols"], "row_round_size": g["row_round_size"],
-           "kernels": kernel_figures(prof, "large", geometry_in_effect(pa, L, 0))}
+           "kernels": kernel_figures(prof, "large", geometry_in_effect(pa, L, 0), L)}
     return res, (k, s, n, m, out.cpu().numpy().view(np.uint64)[: wl.words(m)].copy())
 
 
@@ -608,7 +619,7 @@ def main():
     torch.cuda.synchronize()
     prof = pa.profile_collect()
     pa.profile_enable(False)
-    kernels = kernel_figures(prof, "plain", geometry_in_effect(pa, L, 0))
+    kernels = kernel_figures(prof, "plain", geometry_in_effect(pa, L, 0), L)
     for name, st in prof.items():
         kernels[name]["share_of_step"] = st["total_ms"] / st["launches"] / ms
     dom = max(kernels, key=lambda k: kernels[k]["avg_us"])
@@ -616,8 +627,8 @@ def main():
     bound = "alu" if kd["alu_frac"] >= kd["hbm_frac"] else "hbm"
     traffic = kd["traffic"]
     if bound == "alu":
-        roofline = {"bound": "alu", "kernel": dom, "achieved": kd["fp64_Tops"], "peak": FP64_VALU_PEAK_TOPS,
-                    "unit": "Tops/s (fp64 FMA/add)", "frac": kd["alu_frac"], "traffic": traffic}
+        roofline = {"bound": "alu", "kernel": dom, "achieved": kd["Tops"], "peak": kd["Tops_peak"],
+                    "unit": "Tops/s (%s)" % kd["ops"], "frac": kd["alu_frac"], "traffic": traffic}
     else:
         roofline = {"bound": "hbm", "kernel": dom, "achieved": kd["hbm_GBs"], "peak": HBM_PEAK_GBS,
                     "unit": "GB/s", "frac": kd["hbm_frac"], "traffic": traffic}
@@ -656,7 +667,7 @@ def main():
         torch.cuda.synchronize()
         bprof = pa.profile_collect()
         pa.profile_enable(False)
-        bk = kernel_figures(bprof, "batched", geometry_in_effect(pa, L, 1))
+        bk = kernel_figures(bprof, "batched", geometry_in_effect(pa, L, 1), L, args.batch)
         batched = {"value": args.batch * n / (bms * 1e-3) / 1e9, "unit": "Gb/s", "blocks": args.batch,
                    "ms_per_batch": bms, "kernels": bk,
                    "speedup_vs_plain": args.batch * n / (bms * 1e-3) / 1e9 / value,
@@ -686,7 +697,7 @@ def main():
                      for i in range(0, args.batch, 16)]
         shared = {"value": args.batch * n / (sms * 1e-3) / 1e9, "unit": "Gb/s", "blocks": args.batch,
                   "ms_per_batch": sms, "speedup_vs_own_seeds": bms / sms,
-                  "kernels": kernel_figures(sprof, "batched_shared_seed", geometry_in_effect(pa, L, 1))}
+                  "kernels": kernel_figures(sprof, "batched_shared_seed", geometry_in_effect(pa, L, 1), L, args.batch)}
         del sblocks, dss
         progress("batched, one shared seed: %.3f ms per %d blocks, %.2f Gb/s" % (sms, args.batch, shared["value"]))
 
@@ -751,7 +762,7 @@ def main():
     line = {
         "metric": METRIC, "value": value, "unit": "Gb/s", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": ms, "higher_is_better": True, "scaling": "weak",
-        "vs_baseline": None, "dtype": "f64", "data": "synthetic",
+        "vs_baseline": None, "dtype": "gf2 (exact bits; fp32 counts)", "data": "synthetic",
         "config": {"workload": "single PA block, plain path: n=1000000 key bits, m=250000 output bits, "
                                "Bernoulli(0.5) key and seed bits, packed uint64", "n": n, "m": m,
                    "transform_len": pa.transform_len(n, m)},

@@ -8,9 +8,10 @@
  * and first column, i.e. by n+m-1 seed bits s, and outputs y = T x mod 2.
  * Convention: T[i][j] = s[i - j + n - 1] (row 0 = s[n-1], ..., s[0]; column
  * 0 = s[n-1], ..., s[n+m-2]), so y_i is coefficient n-1+i of the integer
- * convolution s * x taken mod 2.  The library computes that convolution
- * exactly with a number-theoretic transform (the exact analogue of the
- * FFT route of Sec. 2.3 Eq. (4)), so the result is bit-exact.
+ * convolution s * x taken mod 2.  The library computes it exactly, over
+ * GF(2) on packed bits or with a number-theoretic transform (the exact
+ * analogue of the FFT route of Sec. 2.3 Eq. (4)), so the result is
+ * bit-exact.
  *
  * Bit arrays: little-endian packed uint64, bit k in word k >> 6 at position
  * k & 63.  key: ceil(n/64) words; seed: ceil((n+m-1)/64) words; out:
@@ -71,7 +72,7 @@ pa_status pa_toeplitz_hash(const uint64_t *key_bits, uint64_t n,
  * allocate device memory: code recorded under HIP stream capture, tight
  * serving loops, harnesses that forbid hipMalloc.  Same arguments, result
  * and stream semantics as pa_toeplitz_hash; the two residue arrays of the
- * block (8 L bytes, L = pa_transform_len(n, m)) live in one static device
+ * block (at most 8 L bytes, L = pa_transform_len(n, m)) live in one static device
  * array of PA_NOALLOC_SCRATCH_BYTES per device, which the library holds
  * from its first use on a device until the process ends.  No part of that
  * array needs clearing: every pass writes all it later reads.
@@ -121,8 +122,9 @@ typedef struct pa_block {
  * seed_bits pointer and seed bit count (n + m - 1) are the same use one
  * seed spectrum, built once in the call, and run only their keys' passes
  * against it; the result is the same, the seed's own passes are saved, and
- * the workspace holds 4 L bytes per such block plus 4 L per shared seed
- * (8 L per block otherwise).  The library matches pointers, not contents.
+ * the workspace holds at most 4 L bytes per such block plus 4 L per shared
+ * seed (8 L per block otherwise); blocks short enough for a direct product
+ * have no spectra.  The library matches pointers, not contents.
  */
 pa_status pa_toeplitz_hash_batched(const pa_block *blocks, uint32_t count,
                                    void *stream);
@@ -212,9 +214,9 @@ pa_status pa_toeplitz_hash_pair_fft(const uint64_t *key_a, const uint64_t *key_b
 uint64_t pa_final_key_length(uint64_t n, uint64_t t, uint64_t s);
 
 /*
- * Seed plans: the transformed seed (spectrum of the seed prefix, scaled by
- * the inverse length) kept resident in HBM so repeated hashes with one
- * seed skip the seed transform.  A plan built from seed_len_bits bits with
+ * Seed plans: the transformed seed (and, for short blocks, a copy of its
+ * bits) kept resident in HBM so repeated hashes with one seed skip the seed
+ * transform.  A plan built from seed_len_bits bits with
  * transform length L serves every (n, m) with n + m - 1 <= seed_len_bits
  * and required length <= L (seed bits beyond n+m-1 never influence y).
  * transform_len = 0 picks the smallest supported L covering any n + m - 1
@@ -247,9 +249,8 @@ pa_status pa_plan_destroy(pa_plan_t plan);
  *   instead of the packed parity window.  The values are exact integers in
  *   [0, min(na, nb)].  out: L int32, device.  Uses the stream's workspace.
  *   PA_ERR_UNSUPPORTED_SIZE for an unsupported length.
- * pa_plan_spectrum: copies the plan's resident seed spectrum to out (L
- *   int32, device, stream-ordered): the length-L number-theoretic
- *   transform of the seed's first min(seed_len_bits, L) bits, values
+ * pa_plan_spectrum: writes the plan's seed spectrum to out (L int32,
+ *   device, stream-ordered): the length-L number-theoretic transform of the seed's first min(seed_len_bits, L) bits, values
  *   reduced to |v| <= P/2 + 4 (P = 27*2^20 + 1), in the transform's own
  *   (digit-reversed) order.
  */
@@ -295,7 +296,7 @@ typedef struct pa_plan_info {
 pa_status pa_plan_describe(uint64_t transform_len, uint32_t log2_rows, uint32_t tile_width, pa_plan_info *info);
 
 /* Device bytes of library workspace one in-flight block of (n, m) needs on
- * the plain path (two length-L residue arrays); 0 if invalid. */
+ * the plain path at most (two length-L residue arrays); 0 if invalid. */
 size_t pa_workspace_bytes(uint64_t n, uint64_t m);
 
 /*
@@ -308,8 +309,10 @@ size_t pa_workspace_bytes(uint64_t n, uint64_t m);
  * transform (row_first: radix-2 stages in its first round plus one; the
  * later rounds share the rest evenly) and a fixed row-pass workgroup size
  * (row_threads: 256, 512, 768 or 1024; otherwise launches choose one by
- * occupancy).  Zero fields take the built-in defaults.  Any valid geometry
- * gives the same bits; the choice only changes speed.  Plans and the
+ * occupancy).  Zero fields take the built-in defaults.  A length whose
+ * geometry is the default computes over GF(2) where that form covers the
+ * block; another geometry selects the number-theoretic transform with it.
+ * Any valid geometry gives the same bits; the choice only changes speed.  Plans and the
  * server's resident seed spectra keep the geometry they were built with.
  *
  * pa_tune_set_geometry: use *g for (transform_len, batch_class) from now
