@@ -760,7 +760,9 @@ __global__ void __launch_bounds__(64 * kGfWaves) k_gf_inv(JobArgs ja, int g) {
 // LDS, nine at a time and once each, so that a word read from memory serves
 // as many outputs as the workgroup has rows of 3 M words (17 at that size);
 // word pairs for even G, whose rotations keep them.  Bound by the LDS reads
-// and the three operations that step an offset modulo 3 M.
+// and the three operations that step an offset modulo 3 M: 53 us.  (64
+// blocks, four ranges each: 41 us, 21.7 staged, 19.8 with a job's ranges on
+// one XCD.)
 // Grid: (ranges of 1024 K V - 2 output words, jobs), 16 waves.
 template <int T, int G, int K>
 struct GfInvMany {
@@ -775,12 +777,20 @@ __global__ void __launch_bounds__(1024) k_gf_inv_many(JobArgs ja) {
     constexpr int M = I::M, V = I::V, NTH = I::NTH, PE = 3 * M, NL = (9 * PE / V + NTH - 1) / NTH;
     static_assert(T % 9 == 0 && PE % V == 0, "nine products a stage");
     typedef typename std::conditional<V == 2, unsigned long long, uint32_t>::type Wv;
-    const JobDesc job = job_of(ja, uni(blockIdx.y));
+    // workgroups go to the eight XCDs in turn, each with an L2 of its own: all
+    // ranges of a job to one (jobs past a multiple of eight: as they come)
+    uint32_t range = blockIdx.x, of = blockIdx.y;
+    if (of < (gridDim.y & ~7u)) {
+        const uint32_t id = range + gridDim.x * of, slot = id >> 3, set = slot / gridDim.x;
+        range = slot - set * gridDim.x;
+        of = set * 8 + (id & 7u);
+    }
+    const JobDesc job = job_of(ja, uni(of));
     const int tid = threadIdx.x;
     const uint32_t first = job.n + gf_lead_bits(job, false) - 1u;  // bit of the product where the output starts
     const int words = (int)((job.m + 63u) / 64u * 2u), W0 = (int)(first / 32u);
     // cyclic word of the range's first (V = 2: even, so that pairs lie in a row)
-    const int base = (W0 & ~(V - 1)) + (int)blockIdx.x * I::step;
+    const int base = (W0 & ~(V - 1)) + (int)range * I::step;
     if (base - W0 >= words) return;
     const rsrc_t h = make_rsrc(job.A + (size_t)T * 2 * M, (uint32_t)(T * 4 * M * 4));
     uint32_t *lds = (uint32_t *)pa_lds;
