@@ -523,6 +523,13 @@ uint64_t area_words_s(const pa::PlanRef &p) {
     return p.host->L;
 }
 
+// Workspace of one block of length L, A and S: the transform's, which the
+// areas of the carry-less forms fit into.  A call asks for it whatever form
+// its sizes take, so that blocks of one length need one workspace: a call
+// under stream capture, where nothing can be allocated, runs after any
+// earlier call of its length.  A resident spectrum leaves half of it.
+static size_t block_bytes(uint64_t L) { return (size_t)(8 * L); }
+
 // Key path against a ready spectrum Shat: P1 (key), P2 (convolve), P3.
 pa_status run_key_path(const pa::PlanRef &p, const uint64_t *key, uint64_t n, uint64_t m, const int32_t *Shat,
                        int32_t *A, uint64_t *out, hipStream_t s) {
@@ -553,12 +560,11 @@ pa_status hash_one(const uint64_t *key, uint64_t n, const uint64_t *seed, uint64
     pa::PlanRef p{};
     PA_TRY(plan_for(L, 0, &p));
     if (gf_allowed(p)) p.gf = pa::gf_plain_for(n, m, pa::required_len(n, m), UINT64_MAX, 1);
-    const uint64_t wa = area_words_a(p), wsd = area_words_s(p);
     void *ws = nullptr;
     std::unique_lock<std::mutex> ws_hold;
-    PA_TRY(get_workspace(s, (size_t)std::max<uint64_t>(4 * (wa + wsd), 256), &ws, &ws_hold));
+    PA_TRY(get_workspace(s, block_bytes(L), &ws, &ws_hold));
     pa::JobArgs ja{};
-    ja.one = plain_job(key, n, seed, m, out, (int32_t *)ws, (int32_t *)ws + wa);
+    ja.one = plain_job(key, n, seed, m, out, (int32_t *)ws, (int32_t *)ws + area_words_a(p));
     return run_plain(p, ja, 1, words8(n) + words8(n + m - 1), words8(m), s);
 }
 
@@ -680,7 +686,7 @@ pa_status pa_plan_describe(uint64_t transform_len, uint32_t log2_rows, uint32_t 
 
 size_t pa_workspace_bytes(uint64_t n, uint64_t m) {
     const uint64_t L = pa_transform_len(n, m);
-    return L ? (size_t)(8 * L) : 0;
+    return L ? block_bytes(L) : 0;
 }
 
 pa_status pa_toeplitz_hash(const uint64_t *key_bits, uint64_t n, const uint64_t *seed_bits, uint64_t m,
@@ -706,12 +712,11 @@ pa_status pa_modified_toeplitz_hash(const uint64_t *key_bits, uint64_t n, const 
     pa::PlanRef p{};
     PA_TRY(plan_for(L, 0, &p));
     if (gf_allowed(p)) p.gf = pa::gf_plain_for(n - m, m, pa::required_len(n - m + pa::kGfLead, m), UINT64_MAX, 1);
-    const uint64_t wa = area_words_a(p), wsd = area_words_s(p);
     void *ws = nullptr;
     std::unique_lock<std::mutex> ws_hold;
-    PA_TRY(get_workspace(s, (size_t)std::max<uint64_t>(4 * (wa + wsd), 256), &ws, &ws_hold));
+    PA_TRY(get_workspace(s, block_bytes(L), &ws, &ws_hold));
     pa::JobArgs ja{};
-    ja.one = modified_job(key_bits, n, v_bits, m, out_bits, (int32_t *)ws, (int32_t *)ws + wa);
+    ja.one = modified_job(key_bits, n, v_bits, m, out_bits, (int32_t *)ws, (int32_t *)ws + area_words_a(p));
     return run_plain(p, ja, 1, words8(n) + words8(n - 1) + words8(m), words8(m), s);
 }
 
@@ -1219,7 +1224,7 @@ pa_status pa_plan_hash(pa_plan_t plan, const uint64_t *key_bits, uint64_t n, uin
         if (c.form == pa::kGfDirect) p.gf = c;
         p.gf.max_m = (uint32_t)m;
     }
-    PA_TRY(get_workspace((hipStream_t)stream, (size_t)std::max<uint64_t>(4 * area_words_a(p), 256), &ws, &ws_hold));
+    PA_TRY(get_workspace((hipStream_t)stream, block_bytes(plan->L) / 2, &ws, &ws_hold));
     if (p.gf.form == pa::kGfDirect) {
         pa::JobArgs ja{};
         ja.one = plain_job(key_bits, n, plan->seed, m, out_bits, (int32_t *)ws, nullptr);
@@ -1257,7 +1262,7 @@ pa_status pa_cyclic_convolution(const uint64_t *a_bits, uint64_t na, const uint6
     PA_TRY(plan_for(L, 0, &p));
     void *ws = nullptr;
     std::unique_lock<std::mutex> ws_hold;
-    PA_TRY(get_workspace(s, (size_t)(8 * L), &ws, &ws_hold));
+    PA_TRY(get_workspace(s, block_bytes(L), &ws, &ws_hold));
     pa::JobArgs ja{};
     pa::JobDesc &j = ja.one;
     j.key = a_bits;
