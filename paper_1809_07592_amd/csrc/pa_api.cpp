@@ -559,7 +559,7 @@ pa_status hash_one(const uint64_t *key, uint64_t n, const uint64_t *seed, uint64
                    hipStream_t s) {
     pa::PlanRef p{};
     PA_TRY(plan_for(L, 0, &p));
-    if (gf_allowed(p)) p.gf = pa::gf_plain_for(n, m, pa::required_len(n, m), UINT64_MAX, 1);
+    if (gf_allowed(p)) p.gf = pa::gf_plain_for(L, n, m, pa::required_len(n, m), UINT64_MAX, 1);
     void *ws = nullptr;
     std::unique_lock<std::mutex> ws_hold;
     PA_TRY(get_workspace(s, block_bytes(L), &ws, &ws_hold));
@@ -577,9 +577,13 @@ struct pa_plan_s {
     int device = 0;
     uint64_t L = 0;
     uint64_t seed_len = 0;
-    int32_t *Shat = nullptr;     // spectrum in lp's form; the plan's allocation
-    uint64_t *seed = nullptr;    // carry-less form: the seed's first min(seed_len, L) bits, after Shat
+    void *mem = nullptr;         // one allocation: the spectra and the seed's copy
+    int32_t *Shat = nullptr;     // the transform's spectrum, where it is the faster one for some blocks
+    int32_t *Sgf = nullptr;      // spectrum of the split form, likewise
+    uint64_t *seed = nullptr;    // the seed's first min(seed_len, L) bits, where a carry-less form can be taken
     pa::PlanRef lp{};
+    pa::GfChoice split{};
+    uint64_t limit = 0;          // the most outputs for which the split form is faster
 };
 
 extern "C" {
@@ -711,7 +715,7 @@ pa_status pa_modified_toeplitz_hash(const uint64_t *key_bits, uint64_t n, const 
     hipStream_t s = (hipStream_t)stream;
     pa::PlanRef p{};
     PA_TRY(plan_for(L, 0, &p));
-    if (gf_allowed(p)) p.gf = pa::gf_plain_for(n - m, m, pa::required_len(n - m + pa::kGfLead, m), UINT64_MAX, 1);
+    if (gf_allowed(p)) p.gf = pa::gf_plain_for(L, n - m, m, pa::required_len(n - m + pa::kGfLead, m), UINT64_MAX, 1);
     void *ws = nullptr;
     std::unique_lock<std::mutex> ws_hold;
     PA_TRY(get_workspace(s, block_bytes(L), &ws, &ws_hold));
@@ -801,19 +805,6 @@ pa_status prepare_batch(const pa_block *blocks, uint32_t count, bool modified, B
         gr.L = g.first;
         gr.members = g.second;
         PA_TRY(plan_for(g.first, g.second.size() > 1 ? 1 : 0, &gr.plan));
-        if (form == kFormLanes && gf_allowed(gr.plan)) {
-            const uint64_t lead = modified ? pa::kGfLead : 0;
-            uint64_t n = 0, m = 0, bits = 0;
-            for (uint32_t i : gr.members) {
-                const uint64_t kn = modified ? blocks[i].n - blocks[i].m : blocks[i].n;
-                n = std::max(n, kn);
-                m = std::max(m, blocks[i].m);
-                bits = std::max(bits, pa::required_len(kn + lead, blocks[i].m));
-            }
-            // a graph's launches keep room for the longest blocks of the length
-            gr.plan.gf = pa::gf_plain_for(n, m, any_sizes ? gr.L + lead : bits, UINT64_MAX, (int)gr.members.size());
-            if (any_sizes) gr.plan.gf.max_m = (uint32_t)(modified ? gr.L : gr.L / 2 + 64);
-        }
         if (form == kFormLanes) {
             // seeds shared by several members of the group (same device
             // pointer and bit count, so the same spectrum), in first-use order
@@ -835,6 +826,22 @@ pa_status prepare_batch(const pa_block *blocks, uint32_t count, bool modified, B
                 else gr.plain.push_back(v[0]);
             }
             njob_descs += gr.shared.size();
+            if (gf_allowed(gr.plan)) {
+                const uint64_t lead = modified ? pa::kGfLead : 0;
+                uint64_t n = 0, m = 0, bits = 0;
+                for (uint32_t i : gr.members) {
+                    const uint64_t kn = modified ? blocks[i].n - blocks[i].m : blocks[i].n;
+                    n = std::max(n, kn);
+                    m = std::max(m, blocks[i].m);
+                    bits = std::max(bits, pa::required_len(kn + lead, blocks[i].m));
+                }
+                // one form for the group: by what most of its blocks are.  A
+                // graph's launches keep room for the longest blocks of the length.
+                const size_t own = gr.plain.size(), all = gr.members.size();
+                gr.plan.gf = pa::gf_plain_for(gr.L, n, m, any_sizes ? gr.L + lead : bits, UINT64_MAX, (int)all,
+                                              2 * own >= all ? pa::kGfBlocks : pa::kGfShared);
+                if (any_sizes) gr.plan.gf.max_m = (uint32_t)(modified ? gr.L : gr.L / 2 + 64);
+            }
         } else {
             gr.plain = gr.members;
         }
@@ -1175,11 +1182,17 @@ pa_status pa_plan_create(const uint64_t *seed_bits, uint64_t seed_len_bits, uint
     // Every block that the plan takes ends within n + m - 1 <= seed_len
     // bits and its required length within L; seed bits past the cyclic
     // length would wrap onto outputs.
-    if (gf_allowed(lp)) lp.gf = pa::gf_split_for(std::min(L, seed_len_bits + 126), UINT64_MAX);
-    const bool gf = lp.gf.form != pa::kGfNone;
-    const size_t spec = (size_t)(4 * area_words_s(lp));
+    // The outputs of later blocks (at most half of L) decide between two
+    // spectra at the lengths where neither is always the faster: both are kept.
+    if (gf_allowed(lp)) p->split = pa::gf_split_for(std::min(L, seed_len_bits + 126), UINT64_MAX);
+    const bool gf = p->split.form != pa::kGfNone;
+    p->limit = pa::gf_split_limit(p->split, L, pa::kGfPlan, 1);
+    pa::PlanRef sp = lp;
+    sp.gf = p->split;
+    const size_t gf_bytes = p->limit > 0 ? (size_t)(4 * area_words_s(sp)) : 0;
+    const size_t ntt_bytes = p->limit < L / 2 ? (size_t)(4 * L) : 0;
     hipError_t e = hipGetDevice(&p->device);
-    if (e == hipSuccess) e = hipMalloc((void **)&p->Shat, spec + (gf ? (size_t)words8(used) : 0));
+    if (e == hipSuccess) e = hipMalloc(&p->mem, gf_bytes + ntt_bytes + (gf ? (size_t)words8(used) : 0));
     if (e != hipSuccess) {
         delete p;
         return from_hip(e, "plan allocation");
@@ -1187,14 +1200,17 @@ pa_status pa_plan_create(const uint64_t *seed_bits, uint64_t seed_len_bits, uint
     p->L = L;
     p->seed_len = seed_len_bits;
     p->lp = lp;
+    if (gf_bytes) p->Sgf = (int32_t *)p->mem;
+    if (ntt_bytes) p->Shat = (int32_t *)((char *)p->mem + gf_bytes);
     if (gf) {
-        p->seed = (uint64_t *)((char *)p->Shat + spec);
+        p->seed = (uint64_t *)((char *)p->mem + gf_bytes + ntt_bytes);
         e = hipMemcpyAsync(p->seed, seed_bits, (size_t)words8(used), hipMemcpyDeviceToDevice, (hipStream_t)stream);
     }
-    pa_status st = e != hipSuccess ? from_hip(e, "plan seed copy")
-                                   : run_seed_path(lp, seed_bits, used, p->Shat, (hipStream_t)stream);
+    pa_status st = e != hipSuccess ? from_hip(e, "plan seed copy") : PA_OK;
+    if (st == PA_OK && p->Sgf) st = run_seed_path(sp, seed_bits, used, p->Sgf, (hipStream_t)stream);
+    if (st == PA_OK && p->Shat) st = run_seed_path(lp, seed_bits, used, p->Shat, (hipStream_t)stream);
     if (st != PA_OK) {
-        (void)hipFree(p->Shat);
+        (void)hipFree(p->mem);
         delete p;
         return st;
     }
@@ -1218,10 +1234,16 @@ pa_status pa_plan_hash(pa_plan_t plan, const uint64_t *key_bits, uint64_t n, uin
     void *ws = nullptr;
     std::unique_lock<std::mutex> ws_hold;
     pa::PlanRef p = plan->lp;
+    const int32_t *spectrum = plan->Shat;
     if (plan->seed) {
         // a short block's product with the seed bits themselves is faster
-        const pa::GfChoice c = pa::gf_plain_for(n, m, plan->L, UINT64_MAX, 1);
-        if (c.form == pa::kGfDirect) p.gf = c;
+        const pa::GfChoice c = pa::gf_plain_for(plan->L, n, m, plan->L, UINT64_MAX, 1);
+        if (c.form == pa::kGfDirect) {
+            p.gf = c;
+        } else if (!spectrum || (plan->Sgf && m <= plan->limit)) {
+            p.gf = plan->split;
+            spectrum = plan->Sgf;
+        }
         p.gf.max_m = (uint32_t)m;
     }
     PA_TRY(get_workspace((hipStream_t)stream, block_bytes(plan->L) / 2, &ws, &ws_hold));
@@ -1230,7 +1252,7 @@ pa_status pa_plan_hash(pa_plan_t plan, const uint64_t *key_bits, uint64_t n, uin
         ja.one = plain_job(key_bits, n, plan->seed, m, out_bits, (int32_t *)ws, nullptr);
         return run_plain(p, ja, 1, words8(n) + words8(n + m - 1), words8(m), (hipStream_t)stream);
     }
-    return run_key_path(p, key_bits, n, m, plan->Shat, (int32_t *)ws, out_bits, (hipStream_t)stream);
+    return run_key_path(p, key_bits, n, m, spectrum, (int32_t *)ws, out_bits, (hipStream_t)stream);
 }
 
 pa_status pa_plan_spectrum(pa_plan_t plan, int32_t *out, void *stream) {
@@ -1238,12 +1260,8 @@ pa_status pa_plan_spectrum(pa_plan_t plan, int32_t *out, void *stream) {
     int dev = 0;
     PA_HIP(hipGetDevice(&dev), "hipGetDevice");
     if (dev != plan->device) return fail(PA_ERR_INVALID_ARG, "plan belongs to another device");
-    if (plan->seed) {
-        // the plan keeps a carry-less spectrum: transform the seed's copy in out
-        pa::PlanRef p = plan->lp;
-        p.gf = pa::GfChoice{};
-        return run_seed_path(p, plan->seed, std::min(plan->seed_len, plan->L), out, (hipStream_t)stream);
-    }
+    if (!plan->Shat)  // only a carry-less spectrum is kept: transform the seed's copy in out
+        return run_seed_path(plan->lp, plan->seed, std::min(plan->seed_len, plan->L), out, (hipStream_t)stream);
     PA_HIP(hipMemcpyAsync(out, plan->Shat, (size_t)(4 * plan->L), hipMemcpyDeviceToDevice, (hipStream_t)stream),
            "spectrum copy");
     return PA_OK;
@@ -1281,7 +1299,7 @@ pa_status pa_cyclic_convolution(const uint64_t *a_bits, uint64_t na, const uint6
 
 pa_status pa_plan_destroy(pa_plan_t plan) {
     if (!plan) return PA_OK;
-    hipError_t e = plan->Shat ? hipFree(plan->Shat) : hipSuccess;
+    hipError_t e = plan->mem ? hipFree(plan->mem) : hipSuccess;
     delete plan;
     return from_hip(e, "hipFree plan");
 }

@@ -49,9 +49,20 @@ constexpr uint64_t kGfLead = 63;
 // `words` 32-bit words; form kGfNone if there is none.
 GfChoice gf_split_for(uint64_t bits, uint64_t words);
 
-// Form for njobs plain blocks of one launch sequence, none longer than n
-// bits, m outputs or a cyclic product of `bits` bits.
-GfChoice gf_plain_for(uint64_t n, uint64_t m, uint64_t bits, uint64_t words, int njobs);
+// What a split product stands in for: blocks with a seed each (one launch
+// sequence), or keys against a spectrum that is there already, of a plan, of a
+// server's seed or of a batch's shared seed.
+enum GfUse { kGfBlocks, kGfPlan, kGfServed, kGfShared };
+
+// The most outputs of a block for which the split product is faster than the
+// transform of length L (0: never; UINT64_MAX: always).
+uint64_t gf_split_limit(const GfChoice &split, uint64_t L, GfUse use, int njobs);
+
+// Form for njobs blocks of one launch sequence, none longer than n bits, m
+// outputs or a cyclic product of `bits` bits, where L is the transform length
+// otherwise; form kGfNone if the transform is faster.
+GfChoice gf_plain_for(uint64_t L, uint64_t n, uint64_t m, uint64_t bits, uint64_t words, int njobs,
+                      GfUse use = kGfBlocks);
 
 // Words of a direct launch's partial results per block (0: one slice).
 inline uint64_t gf_direct_words(const GfChoice &c) {

@@ -68,7 +68,7 @@ extern "C" pa_status pa_toeplitz_hash_noalloc(const uint64_t *key_bits, uint64_t
                                                  std::to_string(kScratchBytes / 8) + ")");
     pa::PlanRef p{};
     PA_TRY(plan_cached(L, 0, &p));
-    if (pa::gf_allowed(p)) p.gf = pa::gf_plain_for(n, m, pa::required_len(n, m), L, 1);
+    if (pa::gf_allowed(p)) p.gf = pa::gf_plain_for(L, n, m, pa::required_len(n, m), L, 1);
     void *base = nullptr;
     PA_TRY(scratch_address(&base));
     int32_t *A = (int32_t *)base;

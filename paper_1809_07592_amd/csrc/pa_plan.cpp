@@ -358,6 +358,66 @@ GfChoice gf_split_for(uint64_t bits, uint64_t words) {
     return GfChoice{};
 }
 
+// Where the transform of length L beats the split size that the bits need.
+// Split sizes are few, and a launch at one costs the same whatever part of
+// the cyclic length is used, plus (T = 729, whose inverse pass reads 729
+// products a word) 7 to 9 us for 10^6 outputs; the transform's time follows L,
+// 13 us for 10^6 points of one block.  Times transform / split, us:
+//
+//   729 chunks, one block, outputs 2% and 50% of the length: L = 3,538,944
+//   54 / 50 and 62, L = 4,718,592 77 / 50 and 64, L = 7,077,888 102 / 105 and
+//   137, L = 9,437,184 138 / 106 and 148, L = 14,155,776 189 / 106 and 170; a
+//   key against a spectrum 42 / 50 and 62, 61 / 50 and 63, 77 / 94 and 128,
+//   110 / 94 and 138, 149 / 95 and 160; each of eight blocks 40 / 25 and 36,
+//   55 / 25 and 40, 87 / 86 and 117, 125 / 88 and 130, 187 / 92 and 154; each
+//   of eight keys on one seed 31 / 24 and 34, 40 / 24 and 39, 65 / 79 and 112,
+//   99 / 80 and 122, 150 / 81 and 146.  So a limit on the outputs, in
+//   sixteenths of L.
+//   629,856 bits, L = 221,184 and 262,144: equal for few blocks, but as long
+//   as the transform's arrays (8 L bytes a block, 4 L with a shared seed) stay
+//   in the 256 MB last-level cache it passes: 32 blocks 81 / 90 and 84 / 91,
+//   64 141 / 153 and 149 / 157, 128 266 / 285 and 305 / 290, 256 625 / 595 and
+//   698 / 610; keys on one seed 8 39 / 40 and 37 / 41, 64 120 / 147 and 129 /
+//   150, 256 460 / 556 and 510 / 550; served requests, 32 at a time, 132 / 150.
+//   209,952 bits, one served request: kernels 13.7 / 15.5 (32: 80 / 67, but no
+//   less from submission to completion).
+//   3,149,280 bits, 10 to 20 keys on one seed (12: 278 / 290 at a third of the
+//   length in outputs; 24, past the cache: 588 / 530).
+uint64_t gf_split_limit(const GfChoice &split, uint64_t L, GfUse use, int njobs) {
+    if (split.form != kGfSplit) return 0;
+    const uint64_t all = UINT64_MAX, points = L * (uint64_t)njobs;
+    if (split.T == 243 && split.g == 1 && L <= 262144) {
+        if (use == kGfServed) return 0;
+        if (use == kGfShared) return njobs < 6 ? all : 0;
+        return use == kGfPlan || njobs < 12 || points > 30000000 ? all : 0;
+    }
+    if (split.T == 81 && split.g == 3) return use == kGfServed ? 0 : all;
+    if (split.T == 243 && split.g == 5)
+        return use == kGfShared && njobs >= 10 && points < 67000000 ? 0 : all;
+    if (split.T != 729) return all;
+    // by blocks: one, two, three to seven, more; one plan key, served keys;
+    // keys on a shared seed: two, three to seven, more
+    static const struct {
+        int g;
+        uint64_t L;
+        int blocks[4], plan, served, shared[3];
+    } limits[] = {{1, 3538944, {4, 7, 16, 16}, 0, 2, {5, 3, 6}},
+                  {1, 4718592, {16, 16, 16, 16}, 6, 16, {16, 16, 16}},
+                  {3, 7077888, {0, 0, 0, 0}, 0, 0, {0, 0, 0}},
+                  {3, 9437184, {6, 5, 5, 7}, 2, 2, {5, 2, 3}},
+                  {3, 14155776, {12, 16, 16, 16}, 6, 6, {16, 16, 16}}};
+    for (const auto &l : limits) {
+        if (l.g != split.g || L > l.L) continue;
+        const int some = njobs <= 2 ? 0 : njobs <= 7 ? 1 : 2;
+        const int s = use == kGfPlan     ? l.plan
+                      : use == kGfServed ? l.served
+                      : use == kGfShared ? l.shared[some]
+                                         : l.blocks[njobs <= 1 ? 0 : 1 + some];
+        return s == 16 ? all : L / 16 * (uint64_t)s;
+    }
+    return all;
+}
+
 // Direct up to where the split form is faster.  One block, back to back (us):
 // n = 200,000 to 50,000 direct 11.5, split 15; 262,144 to 65,536 12.1 and 15;
 // 300,000 to 60,000 15 and 15.  Several blocks cost the direct form about
@@ -376,13 +436,13 @@ GfChoice gf_split_for(uint64_t bits, uint64_t words) {
 // with two, 34.6 with four).  Longer keys leave too few workgroups, and a
 // serial chain in each, unless they are sliced (200,000 to 50,000: 14.6
 // unsliced, 11.7 with four tiles and eight slices).
-GfChoice gf_plain_for(uint64_t n, uint64_t m, uint64_t bits, uint64_t words, int njobs) {
+GfChoice gf_plain_for(uint64_t L, uint64_t n, uint64_t m, uint64_t bits, uint64_t words, int njobs, GfUse use) {
     GfChoice split = gf_split_for(bits, words);
     split.max_m = (uint32_t)m;
     const double products = (double)n * (double)m;
     double most = 1.75e10;
     if (njobs > 1 && split.form == kGfSplit) most = std::min(4.0e9, 1.2e4 * (double)split.cyclic_bits());
-    if (products > most) return split;
+    if (products > most) return m <= gf_split_limit(split, L, use, njobs) ? split : GfChoice{};
     GfChoice c;
     c.form = kGfDirect;
     c.max_m = (uint32_t)m;

@@ -100,6 +100,7 @@ struct Req {
     uint32_t seed;
     const uint64_t *key;
     uint64_t n, m, L, need, ws_off = 0;
+    bool split = false;        // against a spectrum of the split form, where one may be taken
     uint64_t *out;
     Clock::time_point t_submit, t_done;
     bool done = false;
@@ -139,6 +140,7 @@ struct Spectrum {
     const uint64_t *bits = nullptr;  // the seed's bits and their count (copied at admission)
     uint64_t bits_len = 0;
     uint64_t L = 0;
+    bool split = false;            // of the split form, if L's geometry is the default
     int32_t *S = nullptr;
     uint64_t off = 0, bytes = 0;   // pool allocation
     pa::PlanRef plan{};
@@ -152,7 +154,7 @@ struct Spectrum {
 struct Seed {
     const uint64_t *bits;
     uint64_t len;
-    std::map<uint64_t, Spectrum> spectra;  // by transform length
+    std::map<std::pair<uint64_t, bool>, Spectrum> spectra;  // by transform length and form
 };
 
 }  // namespace
@@ -221,7 +223,7 @@ bool pa_server_s::evict_one_locked(const Spectrum *keep) {
     st.spectra_resident--;
     st.spectra_evicted++;
     if (best->ready) spare_events.push_back(best->ready);
-    best_seed->spectra.erase(best->L);
+    best_seed->spectra.erase({best->L, best->split});
     return true;
 }
 
@@ -235,7 +237,7 @@ bool pa_server_s::admit_locked(Req *r, std::vector<Spectrum *> *builds) {
     const uint64_t sbytes = 4 * r->L;
     for (;;) {
         // looked up on every pass: an eviction erases map entries
-        auto it = sd.spectra.find(r->L);
+        auto it = sd.spectra.find({r->L, r->split});
         const bool have = it != sd.spectra.end();
         uint64_t off = 0, soff = 0;
         if (pool->alloc(r->need, &off)) {
@@ -245,11 +247,12 @@ bool pa_server_s::admit_locked(Req *r, std::vector<Spectrum *> *builds) {
                 if (have) {
                     sp = &it->second;
                 } else {
-                    sp = &sd.spectra[r->L];
+                    sp = &sd.spectra[{r->L, r->split}];
                     sp->seed = r->seed;
                     sp->bits = sd.bits;
                     sp->bits_len = sd.len;
                     sp->L = r->L;
+                    sp->split = r->split;
                     sp->off = soff;
                     sp->bytes = sbytes;
                     sp->S = sim ? nullptr : (int32_t *)((char *)pool_base + soff);
@@ -268,6 +271,9 @@ bool pa_server_s::admit_locked(Req *r, std::vector<Spectrum *> *builds) {
     }
 }
 
+// The split size of requests of length L against a seed of `len` bits.
+static pa::GfChoice served_split(uint64_t L, uint64_t len) { return pa::gf_split_for(std::min(L, len + 126), L); }
+
 // Enqueues the spectrum build on the build stream and records its event;
 // nothing waits for it here.
 pa_status pa_server_s::build_spectrum(Spectrum *sp) {
@@ -280,7 +286,7 @@ pa_status pa_server_s::build_spectrum(Spectrum *sp) {
     PA_TRY(plan_for(sp->L, 1, &p));
     // requests of this length end within L; seed bits past the cyclic length
     // would wrap onto outputs.  Areas are 4 L bytes in every form.
-    if (gf_allowed(p)) p.gf = pa::gf_split_for(std::min(sp->L, sp->bits_len + 126), sp->L);
+    if (sp->split && gf_allowed(p)) p.gf = served_split(sp->L, sp->bits_len);
     sp->plan = p;
     PA_TRY(run_seed_path(p, sp->bits, std::min(sp->bits_len, sp->L), sp->S, plan_stream));
     hipError_t e = take_event(&sp->ready);
@@ -533,7 +539,7 @@ void pa_server_s::loop() {
                         pool->release(sp->off, sp->bytes);
                         st.spectrum_bytes -= sp->bytes;
                         st.spectra_resident--;
-                        seeds[sp->seed].spectra.erase(sp->L);
+                        seeds[sp->seed].spectra.erase({sp->L, sp->split});
                     }
                 for (Part &pt : b.parts)
                     if (pt.ev) spare_events.push_back(pt.ev);
@@ -642,6 +648,7 @@ pa_status pa_server_submit(pa_server_t s, uint32_t seed_id, const uint64_t *key_
     r->out = out_bits;
     r->L = L;
     r->need = need;
+    r->split = m <= pa::gf_split_limit(served_split(L, s->seeds[seed_id].len), L, pa::kGfServed, 1);
     r->t_submit = Clock::now();
     *ticket = r->ticket;
     s->pending.push_back(r.get());

@@ -292,7 +292,7 @@ pa_status pa_autotune(uint64_t transform_len, uint32_t count, uint32_t reps, voi
             return fail(PA_ERR_DEVICE, e.what());
         }
         // the default geometry stands for what untuned calls run
-        if (pa::gf_allowed(p)) p.gf = pa::gf_plain_for(n, m, pa::required_len(n, m), L, (int)count);
+        if (pa::gf_allowed(p)) p.gf = pa::gf_plain_for(L, n, m, pa::required_len(n, m), L, (int)count);
         PA_TRY(run_plain(p, ja, (int)count, in_b, out_b, s));  // warm-up
         std::vector<double> t;
         for (uint32_t r = 0; r < reps; ++r) {
