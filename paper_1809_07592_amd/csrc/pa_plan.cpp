@@ -435,14 +435,18 @@ uint64_t gf_split_limit(const GfChoice &split, uint64_t L, GfUse use, int njobs)
 // 25,001: 8.9 with one, 10.8 with four; 32 blocks of 100,000 to 20,000: 57
 // with two, 34.6 with four).  Longer keys leave too few workgroups, and a
 // serial chain in each, unless they are sliced (200,000 to 50,000: 14.6
-// unsliced, 11.7 with four tiles and eight slices).
+// unsliced, 11.7 with four tiles and eight slices).  An unsliced key of more
+// than five chunks a wave in more than one workgroup a CU is slower than the
+// split form and the transform (modified, 100,000 to 140,000: 16.4 against
+// 13.1 and 15.2; 80,000 to 160,000: 12.6 against 13.1).
 GfChoice gf_plain_for(uint64_t L, uint64_t n, uint64_t m, uint64_t bits, uint64_t words, int njobs, GfUse use) {
     GfChoice split = gf_split_for(bits, words);
     split.max_m = (uint32_t)m;
     const double products = (double)n * (double)m;
     double most = 1.75e10;
     if (njobs > 1 && split.form == kGfSplit) most = std::min(4.0e9, 1.2e4 * (double)split.cyclic_bits());
-    if (products > most) return m <= gf_split_limit(split, L, use, njobs) ? split : GfChoice{};
+    const bool long_chain = njobs == 1 && n + 15 > 5 * 16 * 1024 && n <= (1u << 17) && m > 256 * 512;
+    if (products > most || long_chain) return m <= gf_split_limit(split, L, use, njobs) ? split : GfChoice{};
     GfChoice c;
     c.form = kGfDirect;
     c.max_m = (uint32_t)m;

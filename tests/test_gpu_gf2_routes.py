@@ -191,7 +191,8 @@ def test_lines_between_split_form_and_transform(use, L, m, jobs, form):
     assert run_use(use, n, m, jobs, L) == form
 
 
-@pytest.mark.parametrize("kn,m,form", [(fill(E, E // 16 * 12), E // 16 * 12, "split"),
+@pytest.mark.parametrize("kn,m,form", [(100_000, 140_000, "split"), (80_000, 160_000, "direct"),
+                                       (120_000, 131_072, "direct"), (fill(E, E // 16 * 12), E // 16 * 12, "split"),
                                        (fill(E, E // 16 * 12 + 1), E // 16 * 12 + 1, "transform")])
 def test_lines_of_long_outputs(kn, m, form):
     assert run_use("modified", kn + m, m, 1, length(kn, m)) == form
