@@ -839,7 +839,7 @@ pa_status prepare_batch(const pa_block *blocks, uint32_t count, bool modified, B
                 // graph's launches keep room for the longest blocks of the length.
                 const size_t own = gr.plain.size(), all = gr.members.size();
                 gr.plan.gf = pa::gf_plain_for(gr.L, n, m, any_sizes ? gr.L + lead : bits, UINT64_MAX, (int)all,
-                                              2 * own >= all ? pa::kGfBlocks : pa::kGfShared);
+                                              2 * own >= all ? pa::kGfBlocks : pa::kGfShared, any_sizes);
                 if (any_sizes) gr.plan.gf.max_m = (uint32_t)(modified ? gr.L : gr.L / 2 + 64);
             }
         } else {

@@ -60,9 +60,10 @@ uint64_t gf_split_limit(const GfChoice &split, uint64_t L, GfUse use, int njobs)
 
 // Form for njobs blocks of one launch sequence, none longer than n bits, m
 // outputs or a cyclic product of `bits` bits, where L is the transform length
-// otherwise; form kGfNone if the transform is faster.
+// otherwise; form kGfNone if the transform is faster.  captured: the launches
+// of a graph, among which one more costs little.
 GfChoice gf_plain_for(uint64_t L, uint64_t n, uint64_t m, uint64_t bits, uint64_t words, int njobs,
-                      GfUse use = kGfBlocks);
+                      GfUse use = kGfBlocks, bool captured = false);
 
 // Words of a direct launch's partial results per block (0: one slice).
 inline uint64_t gf_direct_words(const GfChoice &c) {

@@ -435,11 +435,15 @@ uint64_t gf_split_limit(const GfChoice &split, uint64_t L, GfUse use, int njobs)
 // 25,001: 8.9 with one, 10.8 with four; 32 blocks of 100,000 to 20,000: 57
 // with two, 34.6 with four).  Longer keys leave too few workgroups, and a
 // serial chain in each, unless they are sliced (200,000 to 50,000: 14.6
-// unsliced, 11.7 with four tiles and eight slices).  An unsliced key of more
+// unsliced, 11.7 with four tiles and eight slices).  In a graph the second
+// launch costs less than a wave's seventh chunk of the key (replays of two
+// blocks of 114,000 to 2,600: 19.1 unsliced, 13.0 sliced, transform 18.0; up
+// to 98,000 equal).  An unsliced key of more
 // than five chunks a wave in more than one workgroup a CU is slower than the
 // split form and the transform (modified, 100,000 to 140,000: 16.4 against
 // 13.1 and 15.2; 80,000 to 160,000: 12.6 against 13.1).
-GfChoice gf_plain_for(uint64_t L, uint64_t n, uint64_t m, uint64_t bits, uint64_t words, int njobs, GfUse use) {
+GfChoice gf_plain_for(uint64_t L, uint64_t n, uint64_t m, uint64_t bits, uint64_t words, int njobs, GfUse use,
+                      bool captured) {
     GfChoice split = gf_split_for(bits, words);
     split.max_m = (uint32_t)m;
     const double products = (double)n * (double)m;
@@ -454,7 +458,7 @@ GfChoice gf_plain_for(uint64_t L, uint64_t n, uint64_t m, uint64_t bits, uint64_
     auto groups = [&](int nt) { return (m + 256 * nt - 1) / (256 * nt) * jobs; };
     c.nt = groups(1) <= 256 ? 1 : njobs == 1 || groups(2) <= 384 ? 2 : 4;
     c.slices = 1;
-    if (n > (1u << 17) && groups(4) < 160) {
+    if (n + 15 > (captured ? 6u * 16 * 1024 : (1u << 17) + 15) && groups(4) < 160) {
         const uint64_t chunks = (n + 15 + 2047) / 2048;  // of 16 steps
         c.nt = 4;
         c.slices = (int)std::min<uint64_t>(320 / groups(4), chunks / 8);

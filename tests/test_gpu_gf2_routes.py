@@ -221,9 +221,11 @@ def test_one_plan_serves_both_spectra():
             pa.tune_set(L, cls, 0, 0)
 
 
-@pytest.mark.parametrize("L,jobs,outputs", [(221_184, 12, (50_003, 101_009, 3_001))])
+@pytest.mark.parametrize("L,jobs,outputs", [(221_184, 12, (50_003, 101_009, 3_001)), (110_592, 2, (2_601, 49_999, 1)),
+                                            (98_304, 2, (1, 2_601, 48_000))])
 def test_graph_updated_within_its_form(L, jobs, outputs):
-    # blocks that take the transform, replayed, then updated to other sizes of their length
+    # blocks that take the transform, or a sliced or unsliced direct product,
+    # replayed, then updated to other sizes of their length
     sets = []
     for m in outputs:
         n = fill(L, m)
