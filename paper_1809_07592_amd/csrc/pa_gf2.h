@@ -11,7 +11,7 @@
 //           2 * 3^a points in the ring of 2 M2 words (M2 = M / 3^a), and
 //           those are multiplied on the matrix cores.
 //
-// Both are exact: every value is a bit, or a count of ones below 2^24 held
+// Both are exact: every value is a bit, or the count of fewer than 2^23 ones
 // in an fp32 accumulator.
 #pragma once
 

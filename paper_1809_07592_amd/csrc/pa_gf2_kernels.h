@@ -42,11 +42,12 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
 // One 16 x 16 x 128 binary product on the matrix cores: the operands hold
 // one bit per fp4 element, ones as 0.5 in one operand where they are 1.0 in
 // the other, so a common one adds 0.5.  Accumulators start at 2^22, whose
-// last place is 0.5: sums stay exact up to 2^23 common ones, and the lowest
-// mantissa bit is the parity.  Lane l holds 32 consecutive k of row (column)
+// last place is 0.5: with fewer than 2^23 common ones (kGfOnes) sums are exact
+// and the lowest mantissa bit is the parity.  Lane l holds 32 consecutive k of row (column)
 // l & 15 from k = 32 (l >> 4), as one 32-bit window; the order of k inside
 // the four registers is free as long as both operands share it.
 constexpr float kGfBias = 4194304.0f;  // 2^22
+constexpr uint64_t kGfOnes = 1u << 23;
 __device__ __forceinline__ gf_v4f bit_mfma(gf_v4i a, gf_v4i b, gf_v4f c) {
     const gf_v8i A = {a[0], a[1], a[2], a[3], 0, 0, 0, 0}, B = {b[0], b[1], b[2], b[3], 0, 0, 0, 0};
     return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A, B, c, 4, 4, 0, 0, 0, 0);
@@ -146,6 +147,7 @@ struct OutWords {
 template <int NT, int ST, int NW, bool PARTS>
 __global__ void __launch_bounds__(64 * NW) k_gf_direct(JobArgs ja) {
     constexpr int U = 2 * NT, SW = 4 * ST + 8 * NT, KW = 4 * ST + 2;  // a chunk's seed and key words
+    static_assert(kMaxLen / NW + 2 * 128 * ST < kGfOnes, "a wave's whole chunks of the longest key");
     const JobDesc job = job_of(ja, uni(blockIdx.z));
     const int n = (int)job.n, R0 = (int)blockIdx.x * NT;
     if ((uint32_t)R0 * 256u >= job.m) return;
@@ -486,6 +488,7 @@ struct GfMul {
     static constexpr int NA = A == 1 ? 3 : A == 2 ? 9 : 27;
     static constexpr int NP = 2 * NA, M = NA * M2, U = M2 / NA;
     static_assert(M2 % NA == 0, "the unit rotation is a whole number of words");
+    static_assert(64 * M2 + 128 < kGfOnes, "a leaf product's counts");
     static constexpr int tiles = (64 * M2 + 255) / 256, steps = (64 * M2 + 16 + 127) / 128;
     // tiles of one sweep over k (their row fragments stay in registers)
     static constexpr int sweeps = (tiles + 6) / 7, nt = (tiles + sweeps - 1) / sweeps;

@@ -461,8 +461,8 @@ GfChoice gf_plain_for(uint64_t L, uint64_t n, uint64_t m, uint64_t bits, uint64_
     if (n + 15 > (captured ? 6u * 16 * 1024 : (1u << 17) + 15) && groups(4) < 160) {
         const uint64_t chunks = (n + 15 + 2047) / 2048;  // of 16 steps
         c.nt = 4;
+        // (at most 320 groups of 32 words: less than any such block's area)
         c.slices = (int)std::min<uint64_t>(320 / groups(4), chunks / 8);
-        if (gf_direct_words(c) > words) c.slices = 1;
     }
     return c;
 }
