@@ -840,7 +840,17 @@ pa_status prepare_batch(const pa_block *blocks, uint32_t count, bool modified, B
                 const size_t own = gr.plain.size(), all = gr.members.size();
                 gr.plan.gf = pa::gf_plain_for(gr.L, n, m, any_sizes ? gr.L + lead : bits, UINT64_MAX, (int)all,
                                               2 * own >= all ? pa::kGfBlocks : pa::kGfShared, any_sizes);
-                if (any_sizes) gr.plan.gf.max_m = (uint32_t)(modified ? gr.L : gr.L / 2 + 64);
+                if (any_sizes) {
+                    pa::GfChoice &gf = gr.plan.gf;
+                    gf.max_m = (uint32_t)(modified ? gr.L : gr.L / 2 + 64);
+                    // the slices' partial results of the most outputs still
+                    // fit the two arrays of the transform
+                    if (gf.slices > 1) {
+                        pa::GfChoice one = gf;
+                        one.slices = 2;
+                        gf.slices = (int)std::min<uint64_t>(gf.slices, 4 * gr.L / gf_direct_words(one));
+                    }
+                }
             }
         } else {
             gr.plain = gr.members;

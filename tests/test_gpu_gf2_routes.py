@@ -243,3 +243,26 @@ def test_graph_updated_within_its_form(L, jobs, outputs):
                 torch.cuda.synchronize()
                 for k, s, b in zip(keys, seeds, blocks):
                     check_windows(host(b[4], m), k, n, s, m)
+
+
+@pytest.mark.parametrize("modified", [False, True])
+def test_graph_memory_is_bounded_by_its_lengths(modified):
+    # a graph keeps room for the most outputs of its blocks' lengths; sliced
+    # direct products of few outputs must not multiply that by their slices
+    L, m = 9_437_184, 60
+    n = fill(L, m)
+    key, seed = dev(wl.random_bits(n + m, wl.rng(102, wl.ROLE_KEY, 0))), dev(wl.random_bits(n + m, wl.rng(102, wl.ROLE_SEED, 0)))
+    out = torch.zeros(1, dtype=torch.int64, device="cuda")
+    blocks = [(key, n + (m if modified else 0), seed, m, out)]
+    with pa.BatchGraph([(key, 5_000, seed, m, out)], modified=modified) as g:  # (what a first graph allocates)
+        g.launch()
+        torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    with pa.BatchGraph(blocks, modified=modified) as g:
+        used = before - torch.cuda.mem_get_info()[0]
+        for _ in range(2):
+            g.launch()
+            torch.cuda.synchronize()
+    assert used <= 8 * L + (32 << 20), used
+    k, s = key.cpu().numpy().view(np.uint64), seed.cpu().numpy().view(np.uint64)
+    check_windows(host(out, m), k, blocks[0][1], s, m, modified)
