@@ -120,6 +120,28 @@ pa_status parse_file(const char *path, std::vector<Row> *rows, const std::string
     return PA_OK;
 }
 
+// Installs the rows of this arch.  A geometry other than the default makes its
+// length compute with the transform, also where an untuned call would compute
+// over GF(2): a file may hold geometries that were timed against the
+// transform's default only, so the log says how many rows do that.
+void install_rows(const char *path, const std::vector<Row> &rows, const std::string &arch) {
+    int used = 0, transform = 0;
+    for (const Row &r : rows) {
+        if (!r.arch.empty() && r.arch != arch) continue;
+        pa::set_tuned_geometry(r.L, (int)r.cls, r.g);
+        ++used;
+        pa::LenPlan def, lp;
+        pa::plan_geometry(r.L, pa::Geometry{}, def);
+        pa::plan_geometry(r.L, r.g, lp);
+        if (!(pa::geometry_of(lp) == pa::geometry_of(def)) && pa::gf_split_for(r.L, UINT64_MAX).form != pa::kGfNone)
+            ++transform;
+    }
+    PA_LOG_AT(LOG_INFO, "tuning cache %s: %d of %zu rows for %s", path, used, rows.size(), arch.c_str());
+    if (transform)
+        PA_LOG_AT(LOG_INFO, "tuning cache %s: %d rows select the transform; autotune those lengths again if the file "
+                  "was written before they could compute over GF(2)", path, transform);
+}
+
 // Writes the current table for `arch` (one line per entry) and keeps the
 // other architectures' lines of an existing file; replaces the file whole.
 pa_status write_file(const char *path, const std::string &arch, bool keep_others) {
@@ -167,13 +189,7 @@ void load_tune_cache_once() {
         const std::string arch = device_arch();
         std::vector<Row> rows;
         if (parse_file(path, &rows, arch) != PA_OK) return;
-        int used = 0;
-        for (const Row &r : rows)
-            if (r.arch.empty() || r.arch == arch) {
-                pa::set_tuned_geometry(r.L, (int)r.cls, r.g);
-                ++used;
-            }
-        PA_LOG_AT(LOG_INFO, "tuning cache %s: %d of %zu rows for %s", path, used, rows.size(), arch.c_str());
+        install_rows(path, rows, arch);
     });
 }
 
@@ -237,8 +253,7 @@ pa_status pa_tune_load(const char *path) {
     const std::string arch = device_arch();
     std::vector<Row> rows;
     PA_TRY(parse_file(path, &rows, arch));
-    for (const Row &r : rows)
-        if (r.arch.empty() || r.arch == arch) pa::set_tuned_geometry(r.L, (int)r.cls, r.g);
+    install_rows(path, rows, arch);
     return PA_OK;
 }
 
