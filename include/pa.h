@@ -216,9 +216,11 @@ uint64_t pa_final_key_length(uint64_t n, uint64_t t, uint64_t s);
 /*
  * Seed plans: the transformed seed (and, for short blocks, a copy of its
  * bits) kept resident in HBM so repeated hashes with one seed skip the seed
- * transform.  A plan built from seed_len_bits bits with
- * transform length L serves every (n, m) with n + m - 1 <= seed_len_bits
- * and required length <= L (seed bits beyond n+m-1 never influence y).
+ * transform.  At the lengths where the number of outputs decides which form
+ * is the faster, a plan keeps the seed in both (up to 4.6 L bytes).  A plan
+ * built from seed_len_bits bits with transform length L serves every (n, m)
+ * with n + m - 1 <= seed_len_bits and required length <= L (seed bits beyond
+ * n+m-1 never influence y).
  * transform_len = 0 picks the smallest supported L covering any n + m - 1
  * <= seed_len_bits.  The plan belongs to the device current at creation;
  * its spectrum is built on `stream`, so hashes on other streams must be
@@ -310,9 +312,9 @@ size_t pa_workspace_bytes(uint64_t n, uint64_t m);
  * later rounds share the rest evenly) and a fixed row-pass workgroup size
  * (row_threads: 256, 512, 768 or 1024; otherwise launches choose one by
  * occupancy).  Zero fields take the built-in defaults.  A length whose
- * geometry is the default computes over GF(2) where that form covers the
- * block; another geometry selects the number-theoretic transform with it.
- * Any valid geometry gives the same bits; the choice only changes speed.  Plans and the
+ * geometry is the default computes over GF(2) where that is faster; another
+ * geometry selects the number-theoretic transform with it.  Any valid
+ * geometry gives the same bits; the choice only changes speed.  Plans and the
  * server's resident seed spectra keep the geometry they were built with.
  *
  * pa_tune_set_geometry: use *g for (transform_len, batch_class) from now

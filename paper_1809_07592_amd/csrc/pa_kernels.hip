@@ -1,8 +1,8 @@
 // gfx950 kernels of the Toeplitz hash.  The forms that compute over GF(2) on
-// packed bits, which default geometries use, are in pa_gf2_kernels.h.  Here:
-// an exact cyclic convolution of the key bits with the seed bits by a
-// number-theoretic transform modulo P = 27*2^20+1, in the four-step layout
-// L = R x C (row-major R x C view):
+// packed bits, which default geometries use where they are the faster, are in
+// pa_gf2_kernels.h.  Here: an exact cyclic convolution of the key bits with
+// the seed bits by a number-theoretic transform modulo P = 27*2^20+1, in the
+// four-step layout L = R x C (row-major R x C view):
 //
 //   P1  k_colfwd      : unpack bits (key shifted to word-align the output),
 //                       length-R forward NTT down each column of a W-wide
