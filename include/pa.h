@@ -216,11 +216,11 @@ uint64_t pa_final_key_length(uint64_t n, uint64_t t, uint64_t s);
 /*
  * Seed plans: the transformed seed (and, for short blocks, a copy of its
  * bits) kept resident in HBM so repeated hashes with one seed skip the seed
- * transform.  At the lengths where the number of outputs decides which form
- * is the faster, a plan keeps the seed in both (up to 4.6 L bytes).  A plan
- * built from seed_len_bits bits with transform length L serves every (n, m)
- * with n + m - 1 <= seed_len_bits and required length <= L (seed bits beyond
- * n+m-1 never influence y).
+ * transform.  Where the number of outputs decides which form is the faster
+ * (transform length 9,437,184) a plan keeps the seed in both, 4.6 L bytes,
+ * elsewhere at most 4.2 L.  A plan built from seed_len_bits bits with
+ * transform length L serves every (n, m) with n + m - 1 <= seed_len_bits and
+ * required length <= L (seed bits beyond n+m-1 never influence y).
  * transform_len = 0 picks the smallest supported L covering any n + m - 1
  * <= seed_len_bits.  The plan belongs to the device current at creation;
  * its spectrum is built on `stream`, so hashes on other streams must be

@@ -1192,8 +1192,8 @@ pa_status pa_plan_create(const uint64_t *seed_bits, uint64_t seed_len_bits, uint
     // Every block that the plan takes ends within n + m - 1 <= seed_len
     // bits and its required length within L; seed bits past the cyclic
     // length would wrap onto outputs.
-    // The outputs of later blocks (at most half of L) decide between two
-    // spectra at the lengths where neither is always the faster: both are kept.
+    // Where the outputs of later blocks (at most half of L) decide which
+    // spectrum is the faster one to use, both are kept.
     if (gf_allowed(lp)) p->split = pa::gf_split_for(std::min(L, seed_len_bits + 126), UINT64_MAX);
     const bool gf = p->split.form != pa::kGfNone;
     p->limit = pa::gf_split_limit(p->split, L, pa::kGfPlan, 1);

@@ -372,7 +372,11 @@ GfChoice gf_split_for(uint64_t bits, uint64_t words) {
 //   55 / 25 and 40, 87 / 86 and 117, 125 / 88 and 130, 187 / 92 and 154; each
 //   of eight keys on one seed 31 / 24 and 34, 40 / 24 and 39, 65 / 79 and 112,
 //   99 / 80 and 122, 150 / 81 and 146.  So a limit on the outputs, in
-//   sixteenths of L.
+//   sixteenths of L.  A plan does not know its outputs, and with a limit it
+//   has to build both spectra: at L = 9,437,184 in 107 us (89 the transform's,
+//   47 the split form's), repaid by two hashes; at L = 4,718,592 and 14,155,776
+//   132 (112, 49) would be for the 4 and 7% that more than six tenths of the
+//   key's bits in outputs lose, so those plans keep the split form's alone.
 //   629,856 bits, L = 221,184 and 262,144: equal for few blocks, but as long
 //   as the transform's arrays (8 L bytes a block, 4 L with a shared seed) stay
 //   in the 256 MB last-level cache it passes: 32 blocks 81 / 90 and 84 / 91,
@@ -402,10 +406,10 @@ uint64_t gf_split_limit(const GfChoice &split, uint64_t L, GfUse use, int njobs)
         uint64_t L;
         int blocks[4], plan, served, shared[3];
     } limits[] = {{1, 3538944, {4, 7, 16, 16}, 0, 2, {5, 3, 6}},
-                  {1, 4718592, {16, 16, 16, 16}, 6, 16, {16, 16, 16}},
+                  {1, 4718592, {16, 16, 16, 16}, 16, 16, {16, 16, 16}},
                   {3, 7077888, {0, 0, 0, 0}, 0, 0, {0, 0, 0}},
                   {3, 9437184, {6, 5, 5, 7}, 2, 2, {5, 2, 3}},
-                  {3, 14155776, {12, 16, 16, 16}, 6, 6, {16, 16, 16}}};
+                  {3, 14155776, {12, 16, 16, 16}, 16, 6, {16, 16, 16}}};
     for (const auto &l : limits) {
         if (l.g != split.g || L > l.L) continue;
         const int some = njobs <= 2 ? 0 : njobs <= 7 ? 1 : 2;

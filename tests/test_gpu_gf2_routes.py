@@ -167,9 +167,9 @@ A, B, C, D, E = 3_538_944, 4_718_592, 7_077_888, 9_437_184, 14_155_776
     ("plain", C, 20_003, 1, "transform"), ("plain", C, C // 2 - 300, 1, "transform"),
     ("plain", D, D // 16 * 6, 1, "split"), ("plain", D, D // 16 * 6 + 1, 1, "transform"),
     ("plain", E, 20_003, 1, "split"), ("plan", A, 20_003, 1, "transform"), ("plan", A, 4_001, 1, "direct"),
-    ("plan", B, B // 16 * 6, 1, "split"), ("plan", B, B // 16 * 6 + 1, 1, "transform"),
+    ("plan", B, B // 2 - 300, 1, "split"),
     ("plan", C, 20_003, 1, "transform"), ("plan", D, D // 8, 1, "split"), ("plan", D, D // 8 + 1, 1, "transform"),
-    ("plan", E, E // 16 * 6, 1, "split"), ("plan", E, E // 16 * 6 + 1, 1, "transform"),
+    ("plan", E, E // 2 - 300, 1, "split"),
     ("serve", 221_184, 20_003, 3, "transform"), ("serve", 294_912, 20_003, 3, "split"),
     ("serve", 131_072, 20_003, 3, "split"), ("serve", 147_456, 20_003, 3, "transform"),
     ("serve", A, A // 8, 3, "split"), ("serve", A, A // 8 + 1, 3, "transform"), ("serve", C, 20_003, 3, "transform"),
