@@ -230,18 +230,25 @@ bool pa_server_s::evict_one_locked(const Spectrum *keep) {
 // Admission of the request at the head of the queue (lock held): its
 // workspace and, if the (seed, length) spectrum is not resident, room for
 // the spectrum, evicting other unused spectra while that helps (never the
-// one this request needs).  New spectra are appended to *builds.  False if
-// the pool cannot hold them yet.
+// one this request needs).  Where there is no room for one of the form it is
+// faster with, but one of the other form is resident, that one serves.  New
+// spectra are appended to *builds.  False if the pool cannot hold them yet.
 bool pa_server_s::admit_locked(Req *r, std::vector<Spectrum *> *builds) {
     Seed &sd = seeds[r->seed];
     const uint64_t sbytes = 4 * r->L;
     for (;;) {
         // looked up on every pass: an eviction erases map entries
         auto it = sd.spectra.find({r->L, r->split});
-        const bool have = it != sd.spectra.end();
+        const auto other = sd.spectra.find({r->L, !r->split});
+        bool have = it != sd.spectra.end();
         uint64_t off = 0, soff = 0;
         if (pool->alloc(r->need, &off)) {
-            if (have || pool->alloc(sbytes, &soff)) {
+            const bool room = have || pool->alloc(sbytes, &soff);
+            if (!room && other != sd.spectra.end()) {
+                it = other;
+                have = true;
+            }
+            if (room || have) {
                 r->ws_off = off;
                 Spectrum *sp = nullptr;
                 if (have) {
@@ -267,7 +274,8 @@ bool pa_server_s::admit_locked(Req *r, std::vector<Spectrum *> *builds) {
             }
             pool->release(off, r->need);
         }
-        if (!evict_one_locked(have ? &it->second : nullptr)) return false;
+        const auto keep = have ? it : other;
+        if (!evict_one_locked(keep != sd.spectra.end() ? &keep->second : nullptr)) return false;
     }
 }
 
